@@ -115,6 +115,67 @@ constexpr int cfg_K_strided(int N, int bytes, int plan = 0, int vb = 8) {
     return first ? first : N;
 }
 
+// Measured geometry of the default strided kernel, for the lengths where the
+// rules above are not the best choice.  The rules count elements per thread;
+// what bounds these tiles is how much of a CU stays busy: a thread count that
+// does not divide every stage's butterflies leaves lanes idle in each stage,
+// radix-3 lengths take a third and fourth stage (one more LDS exchange each)
+// under radix <= 16, and tiles of 24 .. 48 elements per thread hold one
+// workgroup per CU at 150-210 VGPRs, or spill.  So: the two-stage schedule
+// with radices up to 32 (plan 0) where it exists and keeps a butterfly per
+// thread in both stages, T a divisor of both butterfly counts, and from 432
+// points on 16-column tiles (128-byte rows of complex64) with two or more
+// workgroups per CU.  Every (T, P, K, plan) with at most 16% idle lanes was
+// timed over a y-like (columns of one plane) and a z-like array of 256 and 64
+// MiB; an entry is the best of the four together and stands where it gains 2%
+// or more.  GB/s (y / z, 256 MiB complex64), rule -> entry: 162 4806/4433 ->
+// 5688/4979, 216 4769/4514 -> 5313/5062, 243 4710/4519 -> 5161/4972, 288
+// 4926/4576 -> 5512/5052, 324 4621/4369 -> 5458/4943, 432 3188/3013 ->
+// 4733/4609, 486 3120/3050 -> 4700/4521, 576 3673/3465 -> 5017/4527, 648
+// 3440/3348 -> 4742/4682, 729 3545/3403 -> 4593/4560, 768 3861/3685 ->
+// 4915/4764, 864 2799/2713 -> 4745/4700, 972 2581/2538 -> 4167/4170, 1024
+// 4686/3630 -> 5047/3855.  (Complex64 tiles of 128 and 256 points keep the
+// rules: 64-column tiles gained 4-7% there but leave the chip short of
+// workgroups on 128^3 and the half spectra of 256^3, which lost 2-6%.)  The
+// 4-byte types gain 3-40% (864: 2.7x) the same way; FP16 values hold half the
+// state and keep the wider tiles.
+struct StridedGeo {
+    int n, T, P, K, plan;
+};
+constexpr StridedGeo kStrided8[] = {   // complex64
+    {72, 3, 64, 1, 0},   {81, 9, 64, 1, 0},   {108, 3, 64, 2, 0},  {162, 9, 64, 2, 0},  {216, 6, 32, 2, 0},
+    {243, 9, 32, 3, 0},  {288, 18, 32, 1, 0}, {324, 18, 32, 2, 0},
+    {432, 12, 16, 2, 1}, {486, 27, 16, 2, 1}, {576, 16, 16, 2, 2}, {648, 27, 16, 2, 0}, {729, 27, 16, 3, 0},
+    {768, 32, 16, 3, 1}, {864, 32, 16, 2, 0}, {972, 27, 16, 2, 0}, {1024, 32, 16, 2, 0}};
+constexpr StridedGeo kStrided4[] = {   // 4-byte storage, FP32 values
+    {36, 3, 64, 1, 0},   {48, 8, 32, 1, 0},   {64, 8, 64, 1, 0},   {72, 9, 32, 1, 0},   {81, 9, 64, 1, 0},
+    {96, 4, 64, 2, 0},   {108, 3, 64, 2, 0},  {128, 4, 64, 2, 0},  {144, 4, 64, 2, 0},  {162, 9, 64, 2, 0},
+    {192, 8, 32, 2, 0},  {216, 6, 32, 2, 0},  {243, 9, 64, 3, 0},  {256, 8, 64, 2, 0},  {288, 18, 32, 1, 0},
+    {324, 18, 32, 2, 0}, {432, 16, 32, 2, 1}, {486, 18, 32, 2, 0}, {576, 16, 32, 2, 2}, {648, 27, 32, 3, 0},
+    {729, 27, 32, 3, 0}, {768, 32, 32, 3, 1}, {864, 32, 32, 3, 0}, {972, 27, 32, 4, 0}};
+constexpr StridedGeo kStrided4m[] = {   // 4-byte storage, FP16 values
+    {72, 9, 64, 1, 0},   {81, 9, 64, 1, 0},   {96, 8, 64, 1, 0},   {108, 12, 64, 1, 0}, {144, 4, 64, 1, 0},
+    {162, 9, 64, 1, 0},  {192, 4, 64, 1, 0},  {216, 6, 64, 1, 0},  {288, 8, 64, 1, 0},  {324, 18, 32, 1, 0},
+    {384, 8, 64, 3, 0},  {432, 24, 32, 1, 0}, {486, 18, 32, 1, 0}, {576, 24, 32, 1, 0}, {648, 14, 32, 2, 0},
+    {729, 27, 32, 3, 0}, {768, 16, 32, 2, 1}, {864, 16, 32, 2, 0}, {972, 27, 32, 2, 0}, {1024, 16, 64, 4, 0}};
+
+// Geometry of the default strided kernel: the measured entry, else the rules.
+constexpr StridedGeo cfg_strided(int N, int bytes, int vb) {
+    if (bytes == 8) {
+        for (const StridedGeo& g : kStrided8)
+            if (g.n == N) return g;
+    } else if (vb == 8) {
+        for (const StridedGeo& g : kStrided4)
+            if (g.n == N) return g;
+    } else {
+        for (const StridedGeo& g : kStrided4m)
+            if (g.n == N) return g;
+    }
+    const int plan = cfg_plan_strided(N, bytes);
+    return {N, cfg_T_strided(N, bytes, plan, vb), cfg_P_strided(N, bytes, plan, vb), cfg_K_strided(N, bytes, plan, vb),
+            plan};
+}
+
 // Longest pencil a single pass handles in each layout.
 constexpr int kMaxContigN = 16384;   // one pencil of 16384 complex in LDS
 constexpr int kMaxStridedN = 1024;
