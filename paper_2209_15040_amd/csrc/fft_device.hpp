@@ -356,6 +356,8 @@ template <class T> __device__ __forceinline__ gptr<T> gstore_at(char* base, uint
 }
 
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 struct IoC64 {   // complex64: FP32 re, FP32 im
     using value_type = float2;
     static constexpr bool scale_at_load = false;
@@ -472,6 +474,8 @@ struct IoF16M {
     using value_type = h16x2;
     static constexpr bool scale_at_load = true;
     static constexpr int bytes = 4;
+    static __device__ __forceinline__ h16x2 unpack(uint32_t w) { return __builtin_bit_cast(h16x2, w); }
+    static __device__ __forceinline__ uint32_t pack(h16x2 v) { return __builtin_bit_cast(uint32_t, v); }
     static __device__ __forceinline__ h16x2 load(const void* p, int64_t i) {
         return __builtin_bit_cast(h16x2, gload_ptr<uint32_t>(p)[i]);
     }
@@ -600,6 +604,9 @@ enum : int {
     kFlagTemporalStore = 2048,  // with kFlagNontemporal: streaming loads but ordinary (cached)
                                 // stores, so partial lines written by neighbouring accesses merge
                                 // in the cache before they reach memory
+    kFlagStage = 4096,      // contiguous layout: the tile's rows move between memory and LDS as
+                            // one contiguous range, whole lines per wave, and the first stage
+                            // reads and the last stage writes LDS (stage_load, stage_store)
 };
 
 // -------------------------------------------------------------- pass args ---
@@ -714,6 +721,9 @@ struct PencilPass {
     static constexpr bool R2C = (FLAGS & kFlagR2C) != 0;
     static constexpr bool C2R = (FLAGS & kFlagC2R) != 0;
     static constexpr bool SOLVEZ = (FLAGS & kFlagSolveZ) != 0;
+    static constexpr bool STAGE = (FLAGS & kFlagStage) != 0;
+    static_assert(!STAGE || (!STRIDED && K == 1 && !REALIN && (FLAGS & kFlagPairs) == 0),
+                  "staged tiles: contiguous pencils, the whole tile in LDS");
     static_assert(!REALIN || !STRIDED, "real input is read by contiguous passes");
     static_assert(!(REALOUT || POISSON) || (STRIDED && !FOURSTEP), "fused outputs are strided direct passes");
     static_assert(!(R2C || C2R) || (!STRIDED && !FOURSTEP && !REALIN && sizeof(V) == 8),
@@ -970,6 +980,126 @@ struct PencilPass {
         return v;
     }
 
+    // Staged tiles (kFlagStage): the tile's rows of W elements (row p at
+    // p*pitch, W = N or the N + 1 bins of a half spectrum) to and from LDS
+    // position lidx(p, e).  Consecutive lanes take consecutive elements, 16
+    // bytes each where the rows are packed (pitch == W) and the tile is
+    // aligned, so every access covers whole lines whatever the pencil length;
+    // direct accesses of a short or unaligned pencil cover parts of lines,
+    // which streaming accesses fetch and write again for each part.
+    static constexpr int VEC = 16 / IO::bytes;
+    // a staged element as it lies in memory (the LDS holds the tile's words
+    // unconverted: half the LDS traffic of FP32 pairs for the 4-byte types)
+    using SW = std::conditional_t<IO::bytes == 8, V, uint32_t>;
+    static __device__ __forceinline__ SW word(u32x4 w, int i) {
+        if constexpr (IO::bytes == 8) return make_float2(__uint_as_float(w[2 * i]), __uint_as_float(w[2 * i + 1]));
+        else return w[i];
+    }
+    static __device__ __forceinline__ void set_word(u32x4& w, int i, SW v) {
+        if constexpr (IO::bytes == 8) {
+            w[2 * i] = __float_as_uint(v.x);
+            w[2 * i + 1] = __float_as_uint(v.y);
+        } else {
+            w[i] = v;
+        }
+    }
+    template <int W>
+    __device__ __forceinline__ static void stage_load(SW* lds, const Ctx& c, const PassArgs& a) {
+        constexpr int TH = T * P, TOT = P * W;
+        const int64_t q0 = c.col - c.p;
+        const int rows = a.C - q0 < P ? (int)(a.C - q0) : P;
+        const int lim = rows * W;
+        const char* const base = static_cast<const char*>(a.src) + q0 * a.os1_in * IO::bytes;
+        if (a.os1_in == W && (reinterpret_cast<uintptr_t>(base) & 15) == 0 && lim % VEC == 0) {
+            constexpr int PER = (TOT / VEC + TH - 1) / TH;
+            u32x4 buf[PER];
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int idx = ((int)threadIdx.x + i * TH) * VEC;
+                if (idx >= lim) continue;
+                if constexpr (NT) buf[i] = __builtin_nontemporal_load(gload_at<u32x4>(base, (uint32_t)idx * IO::bytes));
+                else buf[i] = *gload_at<u32x4>(base, (uint32_t)idx * IO::bytes);
+            }
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int idx = ((int)threadIdx.x + i * TH) * VEC;
+                if (idx >= lim) continue;
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) lds[lidx((idx + k) / W, (idx + k) % W)] = word(buf[i], k);
+            }
+            return;
+        }
+        constexpr int PER = (TOT + TH - 1) / TH;
+        const uint32_t pitch = (uint32_t)a.os1_in;
+#pragma unroll 4
+        for (int i = 0; i < PER; ++i) {
+            const int idx = (int)threadIdx.x + i * TH;
+            if (idx >= lim) continue;
+            const int p = idx / W, e = idx % W;
+            const uint32_t at = ((uint32_t)p * pitch + (uint32_t)e) * IO::bytes;
+            if constexpr (IO::bytes == 8) lds[lidx(p, e)] = IO::template ld<NT>(base, at);
+            else lds[lidx(p, e)] = NT ? __builtin_nontemporal_load(gload_at<SW>(base, at)) : *gload_at<SW>(base, at);
+        }
+    }
+    template <int W>
+    __device__ __forceinline__ static void stage_store(const SW* lds, const Ctx& c, const PassArgs& a) {
+        constexpr int TH = T * P, TOT = P * W;
+        const int64_t q0 = c.col - c.p;
+        const int rows = a.C - q0 < P ? (int)(a.C - q0) : P;
+        const int lim = rows * W;
+        char* const base = static_cast<char*>(a.dst) + q0 * a.os1_out * IO::bytes;
+        if (a.os1_out == W && (reinterpret_cast<uintptr_t>(base) & 15) == 0 && lim % VEC == 0) {
+            constexpr int PER = (TOT / VEC + TH - 1) / TH;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int idx = ((int)threadIdx.x + i * TH) * VEC;
+                if (idx >= lim) continue;
+                u32x4 w;
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) set_word(w, k, lds[lidx((idx + k) / W, (idx + k) % W)]);
+                if constexpr (NTS) __builtin_nontemporal_store(w, gstore_at<u32x4>(base, (uint32_t)idx * IO::bytes));
+                else *gstore_at<u32x4>(base, (uint32_t)idx * IO::bytes) = w;
+            }
+            return;
+        }
+        constexpr int PER = (TOT + TH - 1) / TH;
+        const uint32_t pitch = (uint32_t)a.os1_out;
+#pragma unroll 4
+        for (int i = 0; i < PER; ++i) {
+            const int idx = (int)threadIdx.x + i * TH;
+            if (idx >= lim) continue;
+            const int p = idx / W, e = idx % W;
+            const uint32_t at = ((uint32_t)p * pitch + (uint32_t)e) * IO::bytes;
+            if constexpr (IO::bytes == 8) IO::template st<NTS>(base, at, lds[lidx(p, e)]);
+            else if constexpr (NTS) __builtin_nontemporal_store(lds[lidx(p, e)], gstore_at<SW>(base, at));
+            else *gstore_at<SW>(base, at) = lds[lidx(p, e)];
+        }
+    }
+    // A staged element as a register value and back.
+    static __device__ __forceinline__ V from_word(SW w) {
+        if constexpr (IO::bytes == 8) return w;
+        else return IO::unpack(w);
+    }
+    static __device__ __forceinline__ SW to_word(V v) {
+        if constexpr (IO::bytes == 8) return v;
+        else return IO::pack(v);
+    }
+    // First-stage inputs from the staged tile (or from values, natural order).
+    template <class L>
+    __device__ __forceinline__ static void lds_first(V* v, const Ctx& c, const L* lds) {
+        using Q = St<0>;
+#pragma unroll
+        for (int t = 0; t < Q::NB; ++t) {
+            const int b = Q::bf(c.j, t);
+            if (!Q::FULL && b >= Q::NBF) continue;
+#pragma unroll
+            for (int r = 0; r < Q::R; ++r) {
+                if constexpr (std::is_same<L, V>::value) v[t * Q::R + r] = lds[lidx(c.p, b + r * Q::NBF)];
+                else v[t * Q::R + r] = from_word(lds[lidx(c.p, b + r * Q::NBF)]);
+            }
+        }
+    }
+
     // kFlagR2C epilogue.  The N-point transform Z of z[m] = a[2m] + i a[2m+1]
     // carries the transforms of the even and odd samples,
     // E = (Z[k] + conj Z[N-k]) / 2 and O = (Z[k] - conj Z[N-k]) / (2i), and
@@ -989,7 +1119,9 @@ struct PencilPass {
             for (int r = 0; r < Q::R; ++r) lds[lidx(c.p, b + r * Q::NBF)] = v[t * Q::R + r];
         }
         __syncthreads();
-        if (!c.valid) return;
+        if constexpr (!STAGE) {
+            if (!c.valid) return;
+        }
         constexpr int H = N / 2;
         constexpr int PER = (H + 1 + T - 1) / T;
         const char* twb = reinterpret_cast<const char*>(a.tw4);
@@ -1006,11 +1138,19 @@ struct PencilPass {
             float2 w = make_float2(wv.x, wv.y);
             if (SIGN > 0) w.y = -w.y;
             const float2 wo = cmul(o, w);
-            gstore(a.dst, c.base_out + k, oscale(cadd(e, wo), a));
-            if (k != N - k) {
-                const float2 m = csub(e, wo);
-                gstore(a.dst, c.base_out + (N - k), oscale(make_float2(m.x, -m.y), a));
+            const float2 lo = oscale(cadd(e, wo), a), m = csub(e, wo);
+            const float2 hi = oscale(make_float2(m.x, -m.y), a);
+            if constexpr (STAGE) {   // in place: only this thread reads or writes bins k and N-k
+                lds[lidx(c.p, k)] = lo;
+                if (k != N - k) lds[lidx(c.p, N - k)] = hi;
+            } else {
+                gstore(a.dst, c.base_out + k, lo);
+                if (k != N - k) gstore(a.dst, c.base_out + (N - k), hi);
             }
+        }
+        if constexpr (STAGE) {
+            __syncthreads();
+            stage_store<N + 1>(reinterpret_cast<const SW*>(lds), c, a);
         }
     }
 
@@ -1026,14 +1166,19 @@ struct PencilPass {
         constexpr int H = N / 2;
         constexpr int PER = (H + 1 + T - 1) / T;
         const char* twb = reinterpret_cast<const char*>(a.tw4);
+        if constexpr (STAGE) {
+            stage_load<N + 1>(reinterpret_cast<SW*>(lds), c, a);
+            __syncthreads();
+        }
         // lanes past the last pencil read the tile's first pencil (never stored)
         const int64_t base = c.valid ? c.base_in : (c.col - c.p) * a.os1_in;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int k = c.j + i * T;
             if (k > H) continue;
-            float2 A = gload(a.src, base + k);
-            float2 Bc = gload(a.src, base + (N - k));
+            // staged: in place, only this thread reads or writes bins k and N-k
+            float2 A = STAGE ? lds[lidx(c.p, k)] : gload(a.src, base + k);
+            float2 Bc = STAGE ? lds[lidx(c.p, N - k)] : gload(a.src, base + (N - k));
             if (k == 0) {
                 A.y = 0.f;
                 Bc.y = 0.f;
@@ -1051,14 +1196,7 @@ struct PencilPass {
             }
         }
         __syncthreads();
-        using Q = St<0>;
-#pragma unroll
-        for (int t = 0; t < Q::NB; ++t) {
-            const int b = Q::bf(c.j, t);
-            if (!Q::FULL && b >= Q::NBF) continue;
-#pragma unroll
-            for (int r = 0; r < Q::R; ++r) v[t * Q::R + r] = lds[lidx(c.p, b + r * Q::NBF)];
-        }
+        lds_first(v, c, lds);
     }
 
     // kFlagSolveZ: after the forward stages, multiply every value by
@@ -1097,6 +1235,20 @@ struct PencilPass {
         using Q = St<S>;
         if constexpr (R2C) {
             store_r2c<S>(lds, v, c, a);
+            return;
+        }
+        if constexpr (STAGE) {
+            __syncthreads();   // the last exchange's reads (or the first stage's) are done
+#pragma unroll
+            for (int t = 0; t < Q::NB; ++t) {
+                const int b = Q::bf(c.j, t);
+                if (!Q::FULL && b >= Q::NBF) continue;
+#pragma unroll
+                for (int r = 0; r < Q::R; ++r)
+                    reinterpret_cast<SW*>(lds)[lidx(c.p, b + r * Q::NBF)] = to_word(oscale(v[t * Q::R + r], a));
+            }
+            __syncthreads();
+            stage_store<N>(reinterpret_cast<const SW*>(lds), c, a);
             return;
         }
         if (FOURSTEP && STRIDED && a.tstore) {
@@ -1274,7 +1426,7 @@ struct PencilPass {
     // (later exchanges always synchronise first).
     template <int S>
     __device__ __forceinline__ static void stages(V* lds, V* v, const Ctx& c, const PassArgs& a,
-                                                  const float2* tw, bool lead0 = C2R) {
+                                                  const float2* tw, bool lead0 = C2R || STAGE) {
         butterflies<S>(v, c.j, tw);
         if constexpr (S + 1 < NS) {
             V w[maxv()];
@@ -1354,7 +1506,7 @@ struct PencilPass {
     // pairs (decided on the unpaired instance: the butterfly counts are the
     // same under both mappings).
     static constexpr bool pairs_help() {
-        return !STRIDED && NT && !REALIN && St<0>::FULL && St<0>::NB % 2 == 0 && St<0>::NBF % 2 == 0;
+        return !STRIDED && !STAGE && NT && !REALIN && St<0>::FULL && St<0>::NB % 2 == 0 && St<0>::NBF % 2 == 0;
     }
 
     // First-stage inputs straight from HBM.
@@ -1433,8 +1585,15 @@ struct PencilPass {
     __device__ __forceinline__ static void run_tile(const PassArgs& a, int64_t t, V* lds) {
         const Ctx c = make_ctx(a, t);
         V v[maxv()];
-        if constexpr (C2R) load_c2r(v, c, a, lds);
-        else load_first(v, c, a);
+        if constexpr (C2R) {
+            load_c2r(v, c, a, lds);
+        } else if constexpr (STAGE) {
+            stage_load<N>(reinterpret_cast<SW*>(lds), c, a);
+            __syncthreads();
+            lds_first(v, c, reinterpret_cast<const SW*>(lds));
+        } else {
+            load_first(v, c, a);
+        }
         scale_loaded(v, a);
         stages<0>(lds, v, c, a, a.tw);
     }

@@ -176,6 +176,84 @@ constexpr StridedGeo cfg_strided(int N, int bytes, int vb) {
             plan};
 }
 
+// Measured geometry of the default contiguous kernel, for the lengths where
+// the rules above are not the best choice.  A direct tile reads and writes
+// T-element pieces of pencils: pieces shorter than a cache line, or of
+// pencils that are no whole lines apart, make streaming accesses fetch and
+// write the same line several times (27 points 1.2 TB/s, 81 points 1.3, 108
+// points 1.2, 32 points 3.5).  Staged tiles (kFlagStage) move the tile's rows
+// as one contiguous range through LDS, whole lines per wave, for two more LDS
+// trips per element; the rest of an entry is as in the strided tables (T a
+// divisor of the stages' butterflies, 64 .. 512 threads).  Direct and staged
+// tiles of every (T, P, plan) were timed at 256 and 32 MiB; staged wins on
+// short and radix-3 lengths, direct from about 500 points on where pencils
+// are whole lines.  GB/s at 256 MiB of complex64, rule -> entry: 16 3236 ->
+// 6281, 27 1191 -> 5823, 32 3546 -> 6235, 36 1290 -> 5849, 64 5903 -> 6183,
+// 81 1296 -> 5880, 96 5299 -> 6096, 108 1175 -> 5718, 144 1908 -> 6034, 192
+// 4237 -> 5899, 216 3898 -> 5919, 243 3782 -> 5418, 288 4440 -> 5781, 324
+// 4617 -> 5829, 384 4845 -> 5796, 432 3950 -> 5253, 486 3939 -> 5562, 512
+// 5792 -> 6104, 576 5281 -> 5790, 648 4048 -> 5616, 768 4548 -> 5889, 864
+// 3911 -> 5404, 972 3891 -> 5020, 4096 5361 -> 5853, 7776 2709 -> 4361.  The
+// FP16-arithmetic entries never have more stages than the rule's schedule
+// (each stage rounds to FP16).
+struct ContigGeo {
+    int n, T, P, plan;
+    bool stage;
+};
+constexpr ContigGeo kContig8[] = {   // complex64
+    {2, 1, 256, 0, true},    {3, 1, 256, 0, true},    {4, 1, 128, 0, true},    {6, 1, 128, 0, true},
+    {8, 1, 256, 0, true},    {9, 1, 256, 0, true},    {12, 1, 64, 2, true},    {16, 1, 64, 2, true},
+    {18, 2, 64, 1, true},    {24, 2, 32, 1, true},    {27, 1, 128, 0, true},   {32, 2, 64, 1, true},
+    {36, 3, 42, 0, true},    {48, 2, 32, 0, true},    {54, 6, 21, 0, true},    {64, 4, 32, 0, true},
+    {72, 9, 28, 0, true},    {81, 9, 28, 0, true},    {96, 8, 16, 0, true},    {108, 9, 14, 2, true},
+    {128, 8, 16, 0, true},   {144, 12, 10, 0, true},  {162, 27, 9, 2, true},   {192, 16, 8, 0, true},
+    {216, 12, 10, 0, true},  {243, 27, 18, 1, true},  {256, 16, 16, 0, true},  {288, 16, 16, 0, true},
+    {324, 18, 14, 0, true},  {384, 16, 4, 0, true},   {432, 24, 5, 0, true},   {486, 54, 9, 1, true},
+    {512, 32, 4, 1, false},  {576, 48, 5, 2, true},   {648, 36, 7, 1, true},   {729, 81, 6, 1, true},
+    {768, 32, 2, 1, false},  {864, 32, 4, 0, false},  {972, 81, 3, 2, true},   {1296, 108, 4, 2, false},
+    {1458, 81, 3, 0, true},  {1728, 96, 2, 2, false}, {1944, 122, 1, 1, true}, {2187, 243, 2, 1, true},
+    {2304, 192, 1, 2, false}, {2592, 144, 1, 0, true}, {2916, 162, 1, 0, true}, {3456, 192, 1, 1, false},
+    {3888, 486, 1, 1, true}, {4096, 256, 1, 2, false}, {4374, 244, 1, 1, false}, {4608, 288, 1, 1, false},
+    {6561, 729, 1, 1, false}, {7776, 432, 1, 0, false}, {8748, 365, 1, 0, false}};
+constexpr ContigGeo kContig4[] = {   // 4-byte storage, FP32 values
+    {2, 1, 256, 0, true},    {3, 1, 256, 0, true},    {6, 1, 64, 0, true},     {8, 1, 64, 0, true},
+    {9, 1, 64, 0, true},     {12, 1, 64, 0, true},    {16, 1, 64, 0, true},    {18, 3, 42, 1, true},
+    {24, 4, 16, 1, true},    {27, 1, 128, 0, true},   {32, 1, 64, 0, true},    {36, 3, 42, 0, true},
+    {48, 4, 16, 0, true},    {54, 6, 42, 0, true},    {64, 8, 8, 0, true},     {72, 9, 7, 0, true},
+    {81, 9, 28, 0, true},    {96, 8, 8, 0, true},     {108, 9, 14, 2, false},  {128, 8, 8, 2, false},
+    {144, 12, 5, 0, true},   {162, 18, 14, 1, true},  {192, 16, 4, 0, true},   {216, 18, 7, 1, false},
+    {243, 27, 18, 1, false}, {256, 16, 4, 2, false},  {288, 18, 7, 0, true},   {324, 18, 7, 0, true},
+    {384, 16, 4, 1, false},  {432, 24, 10, 0, false}, {486, 54, 9, 1, false},  {576, 24, 10, 0, false},
+    {648, 27, 9, 0, false},  {729, 81, 3, 1, false},  {768, 32, 2, 1, false},  {864, 32, 4, 0, false},
+    {972, 81, 3, 2, false},  {1024, 32, 2, 0, false}, {2048, 128, 1, 2, false}};
+constexpr ContigGeo kContig4m[] = {   // 4-byte storage, FP16 values
+    {2, 1, 256, 0, true},    {3, 1, 256, 0, true},    {6, 1, 256, 0, true},    {8, 1, 128, 0, true},
+    {9, 1, 64, 0, true},     {12, 1, 64, 0, true},    {16, 1, 64, 0, true},    {18, 1, 128, 0, true},
+    {24, 2, 32, 1, true},    {27, 1, 64, 0, true},    {32, 4, 32, 1, true},    {36, 3, 21, 0, true},
+    {48, 4, 16, 0, true},    {54, 6, 42, 0, true},    {64, 8, 16, 0, true},    {72, 4, 16, 0, true},
+    {81, 9, 28, 0, true},    {96, 8, 8, 0, true},     {108, 12, 10, 0, true},  {128, 8, 32, 0, true},
+    {144, 12, 10, 0, true},  {162, 9, 14, 0, true},   {192, 16, 8, 0, true},   {216, 12, 10, 0, true},
+    {243, 9, 28, 0, true},   {256, 16, 16, 0, true},  {288, 18, 7, 0, true},   {324, 18, 7, 0, true},
+    {384, 16, 4, 1, false},  {432, 24, 5, 0, true},   {486, 27, 18, 1, true},  {648, 36, 7, 1, true},
+    {729, 27, 9, 0, false},  {768, 32, 2, 1, false},  {864, 32, 2, 0, false},  {1024, 32, 8, 0, false},
+    {2048, 64, 1, 0, false}};
+
+// Geometry of the default contiguous kernel: the measured entry, else the rules.
+constexpr ContigGeo cfg_contig(int N, int bytes, int vb) {
+    if (bytes == 8) {
+        for (const ContigGeo& g : kContig8)
+            if (g.n == N) return g;
+    } else if (vb == 8) {
+        for (const ContigGeo& g : kContig4)
+            if (g.n == N) return g;
+    } else {
+        for (const ContigGeo& g : kContig4m)
+            if (g.n == N) return g;
+    }
+    const int plan = cfg_plan_contig(N, bytes);
+    return {N, cfg_T_contig(N, plan), cfg_P_contig(N, plan, bytes, vb), plan, false};
+}
+
 // Longest pencil a single pass handles in each layout.
 constexpr int kMaxContigN = 16384;   // one pencil of 16384 complex in LDS
 constexpr int kMaxStridedN = 1024;
