@@ -110,15 +110,18 @@ typedef enum {
 #define WSFFT_FLAG_NO_PLANE 8u
 /* Infinity Cache policy.  3D plans of three single passes (x, y, z) by
  * default route data through the 256 MB Infinity Cache by array size A:
- * 64 MiB < A <= 128 MiB (WSFFT_C64 only): every pass with cached loads and
- * stores (the next pass reads its input from the cache); 128 MiB < A <=
- * 256 MiB: the x pass with cached stores; A > 256 MiB: the x and y passes run
- * chunk by chunk over groups of xy-planes of at most 256 MiB, the x pass of a
- * chunk with cached stores, so that its y pass reads the chunk from the cache
- * (the z pass then runs once over the whole array).  Results are bitwise
- * equal to the streaming schedule; only the memory traffic differs.  This
- * flag keeps every pass streaming (non-temporal loads and stores, no
- * chunks). */
+ * 64 MiB < A <= 128 MiB (WSFFT_C64; 16-bit storage 64 MiB <= A < 128 MiB,
+ * its x loads streaming): every pass with cached loads and stores (the next
+ * pass reads its input from the cache); 128 MiB < A <= 256 MiB: the x pass
+ * with cached stores; A > 256 MiB: the x and y passes run chunk by chunk over
+ * groups of xy-planes of at most 256 MiB, the x pass of a chunk with cached
+ * stores, so that its y pass reads the chunk from the cache
+ * (the z pass then runs once over the whole array).  Strided passes whose
+ * rows are no whole 128-byte cache lines go through the caches at every size,
+ * so that neighbouring tiles share the lines at the ends of their rows.
+ * Results are bitwise equal to the streaming schedule; only the memory
+ * traffic differs.  This flag keeps every pass streaming (non-temporal loads
+ * and stores, no chunks). */
 #define WSFFT_FLAG_STREAMING 16u
 
 /*

@@ -652,7 +652,7 @@ struct ArrayDesc {
     int64_t C, O1, es, os1;
     int64_t tile_end;
     float scale;
-    int32_t pad;
+    int32_t flat_c;     // see PassArgs
 };
 constexpr int kMaxBatchDescs = 40;
 struct BatchTable {
@@ -1624,6 +1624,7 @@ struct PencilPass {
             a.es_in = a.es_out = d.es;
             a.os1_in = a.os1_out = d.os1;
             a.scale = d.scale;
+            a.flat_c = d.flat_c;
             t -= i ? bt.d[i - 1].tile_end : 0;
         }
         run_tile(a, t, lds);

@@ -62,11 +62,11 @@ const PassKernel* find_fused_c64_pos(int n, bool strided, int fused);
 const PassKernel* find_real_c64_neg(int n, bool strided, int fused);
 const PassKernel* find_real_c64_pos(int n, bool strided, int fused);
 // Passes that go through the caches (kind kFusedCached: cached loads and
-// stores, both layouts, complex64 only; kFusedCachedStore: contiguous,
-// streaming loads and cached stores, every storage type).  NULL when none
-// exists.
-const PassKernel* find_cached_kernel(StorageKind kind, int sign, int n, bool strided, int fused);
-#define WSFFT_DECLARE_CACHED(NAME) const PassKernel* NAME(int n, bool strided, int fused);
+// stores, strided for every storage type, contiguous for complex64;
+// kFusedCachedStore: contiguous, streaming loads and cached stores, every
+// storage type), variant 0 or 2.  NULL when none exists.
+const PassKernel* find_cached_kernel(StorageKind kind, int sign, int n, bool strided, int fused, int variant = 0);
+#define WSFFT_DECLARE_CACHED(NAME) const PassKernel* NAME(int n, bool strided, int fused, int variant);
 WSFFT_DECLARE_CACHED(find_cached_c64_neg)
 WSFFT_DECLARE_CACHED(find_cached_c64_pos)
 WSFFT_DECLARE_CACHED(find_cached_f16_neg)

@@ -138,18 +138,19 @@ constexpr int cfg_K_strided(int N, int bytes, int plan = 0, int vb = 8) {
 // rules: 64-column tiles gained 4-7% there but leave the chip short of
 // workgroups on 128^3 and the half spectra of 256^3, which lost 2-6%.)  The
 // 4-byte types gain 3-40% (864: 2.7x) the same way; FP16 values hold half the
-// state and keep the wider tiles.
+// state and keep the wider tiles.  (Launches of few 64-column tiles take
+// half-width ones, wsfft_api.hip.)
 struct StridedGeo {
     int n, T, P, K, plan;
 };
 constexpr StridedGeo kStrided8[] = {   // complex64
-    {72, 3, 64, 1, 0},   {81, 9, 64, 1, 0},   {108, 3, 64, 2, 0},  {162, 9, 64, 2, 0},  {216, 6, 32, 2, 0},
+    {72, 9, 32, 1, 0},   {81, 9, 32, 1, 0},   {162, 9, 32, 1, 0},  {216, 6, 32, 2, 0},
     {243, 9, 32, 3, 0},  {288, 18, 32, 1, 0}, {324, 18, 32, 2, 0},
     {432, 12, 16, 2, 1}, {486, 27, 16, 2, 1}, {576, 16, 16, 2, 2}, {648, 27, 16, 2, 0}, {729, 27, 16, 3, 0},
     {768, 32, 16, 3, 1}, {864, 32, 16, 2, 0}, {972, 27, 16, 2, 0}, {1024, 32, 16, 2, 0}};
 constexpr StridedGeo kStrided4[] = {   // 4-byte storage, FP32 values
     {36, 3, 64, 1, 0},   {48, 8, 32, 1, 0},   {64, 8, 64, 1, 0},   {72, 9, 32, 1, 0},   {81, 9, 64, 1, 0},
-    {96, 4, 64, 2, 0},   {108, 3, 64, 2, 0},  {128, 4, 64, 2, 0},  {144, 4, 64, 2, 0},  {162, 9, 64, 2, 0},
+    {96, 4, 64, 2, 0},   {108, 3, 64, 2, 0},  {128, 8, 64, 2, 0},  {144, 4, 64, 2, 0},  {162, 9, 64, 2, 0},
     {192, 8, 32, 2, 0},  {216, 6, 32, 2, 0},  {243, 9, 64, 3, 0},  {256, 8, 64, 2, 0},  {288, 18, 32, 1, 0},
     {324, 18, 32, 2, 0}, {432, 16, 32, 2, 1}, {486, 18, 32, 2, 0}, {576, 16, 32, 2, 2}, {648, 27, 32, 3, 0},
     {729, 27, 32, 3, 0}, {768, 32, 32, 3, 1}, {864, 32, 32, 3, 0}, {972, 27, 32, 4, 0}};

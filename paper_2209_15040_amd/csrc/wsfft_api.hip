@@ -63,6 +63,10 @@ struct Pass {
     int outer_dim;                // count whose stride spans whole arrays: 0 = C, 1 = O1, 2 = O2
     int variant;                  // kernel launch variant (autotuner)
     dim3 grid;
+    // half-width tiles for launches too small to fill the chip with the
+    // default ones (null: none), same radix plan
+    const PassKernel* narrow_neg = nullptr;
+    const PassKernel* narrow_pos = nullptr;
     bool plane = false;           // fused x + y pass over whole planes (n = nx, n2 = ny;
     int64_t n2 = 0;               // tw_off / tw4_off: the x / y stage tables)
     // plane chunks (Infinity Cache policy): C per xy-plane (0: O1 counts the
@@ -252,6 +256,21 @@ void set_four_step(Pass& A, Pass& B, const AxisGeo& g, int64_t n1, int64_t n2) {
         b.os2_in = b.os2_out = I * n;
         b.cs_out = 1;
     }
+}
+
+// A direct pass whose columns leave a ragged tile at every outer index (a
+// sixth of a tile or more idle per sixteen columns of work, counted as 6% of
+// the columns) runs its tiles on across the outer indices instead: 96 columns
+// in 64-column tiles 4.3 -> 4.9 TB/s, 288 in 64 5.6 -> 5.9 (2^25 elements);
+// with less waste the ends of rows cost as much as the idle lanes (729
+// columns in 32: no difference).
+void flatten(PassArgs& a, int per) {
+    if (a.flat_c != 0 || a.O1 <= 1 || a.O2 != 1 || a.C % per == 0 || a.cs_out != 1) return;
+    if (a.tw4_mode != 0 || a.tstore != 0 || a.es_in != a.es_out || a.os1_in != a.os1_out) return;
+    if (a.C > INT32_MAX || ((a.C + per - 1) / per * per - a.C) * 100 < 6 * a.C) return;
+    a.flat_c = a.C;
+    a.C *= a.O1;
+    a.O1 = 1;
 }
 
 int64_t blocks_for(const Pass& P, const PassKernel* k) {
@@ -644,16 +663,38 @@ namespace {
 //    pass reads the chunk from the cache (512^3: 4 chunks, 1107 against
 //    1146 us; 1024^3: 32 chunks, 10.37 against 11.13 ms); chunks of a larger
 //    share of the cache, or streaming x stores, lose it again.
-// The 16-bit storage types have cached-store x kernels only (no cached
-// loads), so they take the last two rules.  The cached kernels have the
-// launch geometry of the default ones, so the results are bitwise equal and
-// the grids unchanged.
+// The 16-bit storage types have no contiguous kernels with cached loads; 64
+// MiB <= A < 128 MiB: cached x stores, cached y and z passes (FP16 256^3 89.4
+// -> 83.8 us, with FP16 arithmetic 84.7 -> 71.6, 512 x 512 x 64 88.7 -> 81.3;
+// at 32 MiB 45 -> 49 and at 512 MiB 611 -> 672, so not there); beyond, the
+// last two rules.  The cached kernels have the launch geometry of the default
+// ones, so the results are bitwise equal.
 bool use_cached(Pass& P, StorageKind kind, int fused) {
     const PassKernel* kn = find_cached_kernel(kind, -1, (int)P.n, P.strided, fused);
     const PassKernel* kp = find_cached_kernel(kind, +1, (int)P.n, P.strided, fused);
     if (!kn || !kp || kn->per_block != P.kern_neg->per_block || kn->threads != P.kern_neg->threads) return false;
     P.kern_neg = kn;
     P.kern_pos = kp;
+    return true;
+}
+
+// Half-width tiles (variant 2) of the default kernels whose tiles are 64
+// columns wide: the launch takes them when the default tiles are fewer than
+// kFillTiles, two per CU.  Below that, wide tiles leave CUs idle (FP16 96 x
+// 144 x 192 25.5 -> 24.6 us, 256^3 89 -> 84 with the cached passes).
+constexpr int64_t kFillTiles = 512;
+bool set_narrow(Pass& P, StorageKind kind) {
+    if (!P.strided || P.plane || P.four_step == 1 || P.variant != 0 || P.kern_neg->per_block < 64) return true;
+    const int fu = P.kern_neg->fused;
+    if (fu != kFusedNone && fu != kFusedCached) return true;
+    const PassKernel* k[2];
+    for (int i = 0; i < 2; ++i)
+        k[i] = fu == kFusedNone ? find_pass_kernel(kind, i ? 1 : -1, (int)P.n, true, false, 2)
+                                : find_cached_kernel(kind, i ? 1 : -1, (int)P.n, true, fu, 2);
+    if (!k[0] || !k[1] || k[0]->plan != P.kern_neg->plan || k[1]->plan != P.kern_neg->plan) return true;
+    if (k[0]->prepare() != hipSuccess || k[1]->prepare() != hipSuccess) return false;
+    P.narrow_neg = k[0];
+    P.narrow_pos = k[1];
     return true;
 }
 
@@ -666,6 +707,14 @@ void apply_cache_policy(wsfft_plan_s* plan) {
         if (ps[i].plane || ps[i].four_step != 0 || ps[i].axis != i || ps[i].strided != (i > 0)) return;
     constexpr int64_t kMiB = int64_t(1) << 20, kCache = 256 * kMiB;
     const int64_t plane = nx * ny * elem_bytes(plan->dtype), A = plane * nz;
+    if (kind != kC64 && A >= 64 * kMiB && A < 128 * kMiB) {
+        Pass q[3] = {ps[0], ps[1], ps[2]};
+        (void)use_cached(q[0], kind, kFusedCachedStore);
+        if (!use_cached(q[1], kind, kFusedCached) || !use_cached(q[2], kind, kFusedCached)) return;
+        for (int i = 0; i < 3; ++i) ps[i] = q[i];
+        plan->cache_mode = 1;
+        return;
+    }
     if (A <= 64 * kMiB) return;
     if (A <= 128 * kMiB) {
         Pass q[3] = {ps[0], ps[1], ps[2]};
@@ -692,6 +741,28 @@ void apply_cache_policy(wsfft_plan_s* plan) {
     ps[0].chunk_c = ny;                    // x: ny pencils per plane
     ps[1].chunk_c = 0;                     // y: planes are its outer index
     for (int i = 0; i < 2; ++i) ps[i].plane_in = ps[i].plane_out = plane;
+}
+}  // namespace
+
+namespace {
+// Strided passes over rows of no whole cache lines (row pitch not a multiple
+// of 128 bytes): neighbouring tiles share the lines at the ends of their
+// rows, which streaming accesses fetch and write once per tile.  Cached loads
+// and stores with each XCD taking a contiguous range of tiles merge them in
+// one L2.  Forward transforms, streaming tiles in natural order -> this rule:
+// complex64 324 x 288 x 216 245 -> 171 us, 243^3 243 -> 138, 486 x 486 x 432
+// 1705 -> 1062, 81 x 512 x 512 469 -> 195 (other passes' gains included;
+// with streaming loads and cached stores 197, 138, 1252 and 209: in place,
+// the cached loads leave the lines in the L2 that the stores then complete);
+// 4-byte passes over 243 columns 2.8 -> 5.2 TB/s, over 324 2.9 -> 5.2.
+void apply_row_policy(std::vector<Pass>& passes, StorageKind kind) {
+    const int64_t eb = kind == kC64 ? 8 : 4;
+    for (Pass& P : passes) {
+        if (!P.strided || P.plane || P.four_step == 1) continue;
+        if ((P.args.es_in * eb) % 128 == 0 && (P.args.O1 == 1 || (P.args.os1_in * eb) % 128 == 0)) continue;
+        if (P.kern_neg->fused == kFusedNone && !use_cached(P, kind, kFusedCached)) continue;
+        P.args.xcd_order = 1;
+    }
 }
 }  // namespace
 
@@ -826,7 +897,10 @@ static wsfft_plan_t plan_create(int64_t nx, int64_t ny, int64_t nz, int dt, int 
         }
         P.grid = dim3((unsigned)blocks);
     }
-    if (!(flags & WSFFT_FLAG_STREAMING)) apply_cache_policy(plan);
+    if (!(flags & WSFFT_FLAG_STREAMING)) {
+        apply_cache_policy(plan);
+        apply_row_policy(plan->passes, kind);
+    }
 
     // buffers: split passes read the caller's input (first) or, for a
     // second split axis, the work buffer
@@ -889,6 +963,13 @@ static wsfft_plan_t plan_create(int64_t nx, int64_t ny, int64_t nz, int dt, int 
         }
     }
     tune_plan(plan, (flags & WSFFT_FLAG_TUNE) != 0);
+    for (Pass& P : plan->passes)
+        if (!set_narrow(P, kind)) {
+            (void)hipFree(plan->tw_dev);
+            if (plan->work) (void)hipFree(plan->work);
+            delete plan;
+            return fail(WSFFT_ERROR_HIP);
+        }
     describe_plan(plan);
     log_plan(plan->desc);
     {
@@ -940,9 +1021,8 @@ wsfft_plan_t wsfft_plan_create_real_ex(int64_t nx, int64_t ny, int64_t nz, unsig
     plan->flags = flags;
     plan->real = true;
     const int64_t N = nx / 2, nxh = N + 1;
-    // half-spectrum row pitch; rows of whole 128-byte lines are aligned
+    // half-spectrum row pitch
     const int64_t hp = half_pitch != 0 ? half_pitch : nxh;
-    const bool aligned = hp % 16 == 0;
     plan->half_pitch = hp;
     TableSet ts;
 
@@ -1006,22 +1086,13 @@ wsfft_plan_t wsfft_plan_create_real_ex(int64_t nx, int64_t ny, int64_t nz, unsig
             ++plan->nsplit;
         }
         // compact rows of the half spectrum are (nx/2 + 1) * 8 bytes apart,
-        // not cache-line aligned: a direct y pass reads and writes through the
-        // caches and each XCD takes a contiguous range of tiles, so tiles that
-        // share lines meet in one L2 (512^3: 238 against 418 us streaming).
-        // Rows padded to whole lines stream (faster there than the cached
-        // pass: 638 against 668 us per R2C + C2R transform at pitch 272).
-        const bool misaligned = g.axis == 1 && !aligned;
+        // not cache-line aligned: a direct pass takes the row policy's cached
+        // kernels and XCD order (512^3, y: 238 against 418 us streaming).
+        // Rows padded to whole lines stream.
         for (Pass& P : ps) {
             P.pass_scale = P.inv_scale = 1.0f;
-            if (misaligned && P.four_step == 0) {
-                P.kern_neg = find_cached_c64_neg((int)P.n, true, kFusedCached);
-                P.kern_pos = find_cached_c64_pos((int)P.n, true, kFusedCached);
-                P.args.xcd_order = 1;
-            } else {
-                P.kern_neg = find_pass_kernel(kC64, -1, (int)P.n, true, P.four_step == 1);
-                P.kern_pos = find_pass_kernel(kC64, +1, (int)P.n, true, P.four_step == 1);
-            }
+            P.kern_neg = find_pass_kernel(kC64, -1, (int)P.n, true, P.four_step == 1);
+            P.kern_pos = find_pass_kernel(kC64, +1, (int)P.n, true, P.four_step == 1);
             if (!P.kern_neg || !P.kern_pos) { delete plan; return fail(WSFFT_ERROR_UNSUPPORTED_SIZE); }
             // a direct pass whose columns leave a ragged tile at every outer
             // index runs its tiles on across the outer indices instead
@@ -1032,6 +1103,7 @@ wsfft_plan_t wsfft_plan_create_real_ex(int64_t nx, int64_t ny, int64_t nz, unsig
                 a.O1 = 1;
             }
         }
+        apply_row_policy(ps, kC64);
         axes.push_back(ps);
     }
     // R2C: x (input -> output), then y, z in place on the output (a split
@@ -1086,7 +1158,7 @@ wsfft_plan_t wsfft_plan_create_real_ex(int64_t nx, int64_t ny, int64_t nz, unsig
         for (Pass& P : *list) {
             set_stage_tw(plan, P);
             P.args.tw4 = P.tw4_off >= 0 ? plan->tw_dev + P.tw4_off : nullptr;
-            if (P.kern_neg->prepare() != hipSuccess || P.kern_pos->prepare() != hipSuccess) {
+            if (P.kern_neg->prepare() != hipSuccess || P.kern_pos->prepare() != hipSuccess || !set_narrow(P, kC64)) {
                 (void)hipFree(plan->tw_dev);
                 if (plan->work) (void)hipFree(plan->work);
                 delete plan;
@@ -1179,28 +1251,26 @@ bool launch_pass(const wsfft_plan_s* plan, size_t pi, const void* in, void* out,
                  hipStream_t stream, int64_t batch = 1, int64_t z0 = 0, int64_t zc = 0) {
     const Pass& P = (plan->real && mode != 0) ? plan->cpasses[pi] : plan->passes[pi];
     PassArgs a = P.args;
-    dim3 grid = P.grid;
+    const int sign = mode == 0 ? plan->sign : -plan->sign;
+    const PassKernel* k = sign < 0 ? P.kern_neg : P.kern_pos;
     int64_t in_off = 0, out_off = 0;   // bytes
     if (zc > 0) {
-        const int64_t per = P.kern_neg->per_block;
         if (P.chunk_c > 0) a.C = P.chunk_c * zc;   // C counts the planes' pencils or columns
         else a.O1 = zc;                           // the outer index counts planes
-        const int64_t blocks = P.strided ? ((a.C + per - 1) / per) * a.O1 * a.O2 : (a.C + per - 1) / per;
-        grid = dim3((unsigned)blocks);
         in_off = z0 * P.plane_in;
         out_off = z0 * P.plane_out;
     }
     if (batch > 1) {   // `batch` arrays back to back: one more factor on the outermost count
-        int64_t blocks;
-        const int64_t per = P.kern_neg->per_block;
         if (P.outer_dim == 0) a.C *= batch;
         else if (P.outer_dim == 1) a.O1 *= batch;
         else a.O2 *= batch;
-        if (P.strided) blocks = ((a.C + per - 1) / per) * a.O1 * a.O2;
-        else blocks = (a.C + per - 1) / per;
-        if (blocks * P.kern_neg->threads > 0xffffffffLL) return false;
-        grid = dim3((unsigned)blocks);
     }
+    auto tiles = [&] { return ((a.C + k->per_block - 1) / k->per_block) * (P.strided ? a.O1 * a.O2 : 1); };
+    if (P.narrow_neg && tiles() < kFillTiles) k = sign < 0 ? P.narrow_neg : P.narrow_pos;
+    if (P.strided) flatten(a, k->per_block);
+    const int64_t blocks = tiles();
+    if (blocks * k->threads > 0xffffffffLL) return false;
+    const dim3 grid((unsigned)blocks);
     auto sel = [&](int s) -> void* {
         return s == 0 ? const_cast<void*>(in) : (s == 1 ? out : plan->work);
     };
@@ -1208,8 +1278,6 @@ bool launch_pass(const wsfft_plan_s* plan, size_t pi, const void* in, void* out,
     a.src = static_cast<const char*>(sel(ip ? P.src_sel_ip : P.src_sel)) + in_off;
     a.dst = static_cast<char*>(sel(ip ? P.dst_sel_ip : P.dst_sel)) + out_off;
     a.scale = mode == 2 ? P.inv_scale : P.pass_scale;
-    const int sign = mode == 0 ? plan->sign : -plan->sign;
-    const PassKernel* k = sign < 0 ? P.kern_neg : P.kern_pos;
     return k->launch(a, nullptr, grid, stream) == hipSuccess;
 }
 
@@ -1425,6 +1493,7 @@ bool launch_level_merged(int count, const wsfft_plan_t* plans, const void* const
                 d.os1 = P.args.os1_in;
                 d.scale = mode == 2 ? P.inv_scale : P.pass_scale;
                 d.tile_end = 0;
+                d.flat_c = (int32_t)P.args.flat_c;
                 if (e == c0) shared = P.args;
             }
             // the tile ranges and stage twiddles of launch kernel kk
@@ -1433,8 +1502,18 @@ bool launch_level_merged(int count, const wsfft_plan_t* plans, const void* const
                 for (size_t e = c0; e < c1; ++e) {
                     const wsfft_plan_s* p = plans[g.idx[e]];
                     const Pass& P = p->passes[pi];
-                    tiles += blocks_for(P, kk);
-                    bt.d[e - c0].tile_end = tiles;
+                    ArrayDesc& d = bt.d[e - c0];
+                    if (P.strided) {
+                        PassArgs a = P.args;
+                        flatten(a, kk->per_block);
+                        d.C = a.C;
+                        d.O1 = a.O1;
+                        d.flat_c = (int32_t)a.flat_c;
+                        tiles += ((a.C + kk->per_block - 1) / kk->per_block) * a.O1 * a.O2;
+                    } else {
+                        tiles += blocks_for(P, kk);
+                    }
+                    d.tile_end = tiles;
                     if (e == c0 && !P.plane) sa.tw = p->tw_dev + P.tw_off + (int64_t)kk->plan * P.n;
                 }
                 return tiles;
@@ -1750,13 +1829,13 @@ const PassKernel* find_pass_kernel(StorageKind kind, int sign, int n, bool strid
     return nullptr;
 }
 
-const PassKernel* find_cached_kernel(StorageKind kind, int sign, int n, bool strided, int fused) {
+const PassKernel* find_cached_kernel(StorageKind kind, int sign, int n, bool strided, int fused, int v) {
     switch (kind) {
-        case kC64: return sign < 0 ? find_cached_c64_neg(n, strided, fused) : find_cached_c64_pos(n, strided, fused);
-        case kF16: return sign < 0 ? find_cached_f16_neg(n, strided, fused) : find_cached_f16_pos(n, strided, fused);
-        case kBF16: return sign < 0 ? find_cached_bf16_neg(n, strided, fused) : find_cached_bf16_pos(n, strided, fused);
+        case kC64: return sign < 0 ? find_cached_c64_neg(n, strided, fused, v) : find_cached_c64_pos(n, strided, fused, v);
+        case kF16: return sign < 0 ? find_cached_f16_neg(n, strided, fused, v) : find_cached_f16_pos(n, strided, fused, v);
+        case kBF16: return sign < 0 ? find_cached_bf16_neg(n, strided, fused, v) : find_cached_bf16_pos(n, strided, fused, v);
         case kF16Math:
-            return sign < 0 ? find_cached_f16m_neg(n, strided, fused) : find_cached_f16m_pos(n, strided, fused);
+            return sign < 0 ? find_cached_f16m_neg(n, strided, fused, v) : find_cached_f16m_pos(n, strided, fused, v);
     }
     return nullptr;
 }
