@@ -134,9 +134,11 @@ constexpr int cfg_K_strided(int N, int bytes, int plan = 0, int vb = 8) {
 // 4733/4609, 486 3120/3050 -> 4700/4521, 576 3673/3465 -> 5017/4527, 648
 // 3440/3348 -> 4742/4682, 729 3545/3403 -> 4593/4560, 768 3861/3685 ->
 // 4915/4764, 864 2799/2713 -> 4745/4700, 972 2581/2538 -> 4167/4170, 1024
-// 4686/3630 -> 5047/3855.  (Complex64 tiles of 128 and 256 points keep the
-// rules: 64-column tiles gained 4-7% there but leave the chip short of
-// workgroups on 128^3 and the half spectra of 256^3, which lost 2-6%.)  The
+// 4686/3630 -> 5047/3855.  256 points keep the rule's tile with the exchange
+// in two rounds, four workgroups per CU instead of two: 5499/5142 ->
+// 5436/5145 at 256 MiB, 5071/4802 -> 5512/5317 at 64.  (Complex64 tiles of
+// 128 and 256 points in 64 columns gained 4-7% there but leave the chip short
+// of workgroups on 128^3 and the half spectra of 256^3, which lost 2-6%.)  The
 // 4-byte types gain 3-40% (864: 2.7x) the same way; FP16 values hold half the
 // state and keep the wider tiles.  (Launches of few 64-column tiles take
 // half-width ones, wsfft_api.hip.)
@@ -145,12 +147,12 @@ struct StridedGeo {
 };
 constexpr StridedGeo kStrided8[] = {   // complex64
     {72, 9, 32, 1, 0},   {81, 9, 32, 1, 0},   {162, 9, 32, 1, 0},  {216, 6, 32, 2, 0},
-    {243, 9, 32, 3, 0},  {288, 18, 32, 1, 0}, {324, 18, 32, 2, 0},
+    {243, 9, 32, 3, 0},  {256, 8, 32, 2, 1},  {288, 18, 32, 1, 0}, {324, 18, 32, 2, 0},
     {432, 12, 16, 2, 1}, {486, 27, 16, 2, 1}, {576, 16, 16, 2, 2}, {648, 27, 16, 2, 0}, {729, 27, 16, 3, 0},
     {768, 32, 16, 3, 1}, {864, 32, 16, 2, 0}, {972, 27, 16, 2, 0}, {1024, 32, 16, 2, 0}};
 constexpr StridedGeo kStrided4[] = {   // 4-byte storage, FP32 values
-    {36, 3, 64, 1, 0},   {48, 8, 32, 1, 0},   {64, 8, 64, 1, 0},   {72, 9, 32, 1, 0},   {81, 9, 64, 1, 0},
-    {96, 4, 64, 2, 0},   {108, 3, 64, 2, 0},  {128, 8, 64, 2, 0},  {144, 4, 64, 2, 0},  {162, 9, 64, 2, 0},
+    {48, 8, 32, 1, 0},   {64, 8, 64, 1, 0},   {72, 9, 32, 1, 0},   {81, 9, 64, 1, 0},
+    {96, 4, 64, 2, 0},   {108, 12, 32, 1, 0},  {128, 8, 64, 2, 0},  {144, 12, 64, 1, 0},  {162, 9, 64, 2, 0},
     {192, 8, 32, 2, 0},  {216, 6, 32, 2, 0},  {243, 9, 64, 3, 0},  {256, 8, 64, 2, 0},  {288, 18, 32, 1, 0},
     {324, 18, 32, 2, 0}, {432, 16, 32, 2, 1}, {486, 18, 32, 2, 0}, {576, 16, 32, 2, 2}, {648, 27, 32, 3, 0},
     {729, 27, 32, 3, 0}, {768, 32, 32, 3, 1}, {864, 32, 32, 3, 0}, {972, 27, 32, 4, 0}};
@@ -159,6 +161,16 @@ constexpr StridedGeo kStrided4m[] = {   // 4-byte storage, FP16 values
     {162, 9, 64, 1, 0},  {192, 4, 64, 1, 0},  {216, 6, 64, 1, 0},  {288, 8, 64, 1, 0},  {324, 18, 32, 1, 0},
     {384, 8, 64, 3, 0},  {432, 24, 32, 1, 0}, {486, 18, 32, 1, 0}, {576, 24, 32, 1, 0}, {648, 14, 32, 2, 0},
     {729, 27, 32, 3, 0}, {768, 16, 32, 2, 1}, {864, 16, 32, 2, 0}, {972, 27, 32, 2, 0}, {1024, 16, 64, 4, 0}};
+
+// Exchange rounds of a split axis's first pass: its FP64 twiddle recurrence
+// restarts in every round, so powers of two take the fewest rounds that leave
+// two workgroups per CU (256 points, 65536 x 1024: one round 414 us, two 439).
+constexpr int cfg_K_four_step(int N, int P, int K, int vb) {
+    if (!is_pow2(N)) return K;
+    for (int k = 1; k < K; ++k)
+        if (N % k == 0 && (N / k) * (P + 1) * vb <= 2 * kLdsRoundBudget) return k;
+    return K;
+}
 
 // Geometry of the default strided kernel: the measured entry, else the rules.
 constexpr StridedGeo cfg_strided(int N, int bytes, int vb) {
