@@ -191,6 +191,13 @@ wsfft_status_t wsfft_execute_inverse(wsfft_plan_t plan, const void* in, void* ou
 wsfft_status_t wsfft_execute_batched(int count, const wsfft_plan_t* plans, const void* const* in,
                                      void* const* out, int adjoint, hipStream_t stream);
 
+/* One plan over `count` arrays stored back to back: array i from in + i arrays
+ * to out + i arrays.  The same result and errors as wsfft_execute_batched with
+ * `count` such entries, one launch per pass, and a cost on the host that does
+ * not grow with `count`. */
+wsfft_status_t wsfft_execute_many(wsfft_plan_t plan, const void* in, void* out, int count, int adjoint,
+                                  hipStream_t stream);
+
 /*
  * Batch-level autotuning (paper Section 5.3 runs many small transforms side
  * by side; here their merged launches are tuned as launched).  Runs the batch

@@ -72,6 +72,7 @@ _execute_batched = _sig("wsfft_execute_batched", _int,
                         [_int, ctypes.POINTER(_vp), ctypes.POINTER(_vp), ctypes.POINTER(_vp), _int, _vp])
 _tune_batched = _sig("wsfft_tune_batched", _int,
                      [_int, ctypes.POINTER(_vp), ctypes.POINTER(_vp), ctypes.POINTER(_vp), _int, _vp])
+_execute_many = _sig("wsfft_execute_many", _int, [_vp, _vp, _vp, _int, _int, _vp])
 _execute_pass = _sig("wsfft_execute_pass", _int, [_vp, _int, _int, _vp, _vp, _vp])
 _scale_log2 = _sig("wsfft_plan_scale_log2", _int, [_vp])
 _num_passes = _sig("wsfft_plan_num_passes", _int, [_vp])
@@ -253,23 +254,16 @@ def tune_batched(plans, ins, outs, adjoint: bool = False, stream=None) -> None:
 
 def execute_many(plan: Plan, x: torch.Tensor, out: torch.Tensor, count: int, adjoint: bool = False,
                  stream=None) -> torch.Tensor:
-    """``wsfft_execute_batched`` over `count` arrays stored back to back in
+    """``wsfft_execute_many`` over `count` arrays stored back to back in
     `x` and `out` (one plan): the single-launch-per-pass batch."""
-    import numpy as np
     per = 1 if plan.dtype == C64 else 2
     for t, nm in ((x, "input"), (out, "output")):
         if not t.is_cuda or t.dtype != _TORCH_DTYPE[plan.dtype] or not t.is_contiguous():
             raise ValueError(f"{nm} must be a contiguous device tensor of the plan's dtype")
         if t.numel() != plan.size * per * count:
             raise ValueError(f"{nm} holds {t.numel()} elements, want {plan.size * per * count}")
-    span = plan.size * (8 if plan.dtype == C64 else 4)
-    offs = np.arange(count, dtype=np.uint64) * np.uint64(span)
-    ins = offs + np.uint64(x.data_ptr())
-    outs = offs + np.uint64(out.data_ptr())
-    hs = np.full(count, plan.handle, dtype=np.uint64)
-    P = ctypes.POINTER(_vp)
-    _check(_execute_batched(count, hs.ctypes.data_as(P), ins.ctypes.data_as(P), outs.ctypes.data_as(P),
-                            int(bool(adjoint)), _stream(stream)), "execute_batched")
+    _check(_execute_many(plan.handle, x.data_ptr(), out.data_ptr(), count, int(bool(adjoint)), _stream(stream)),
+           "execute_batched")
     return out
 
 

@@ -1804,6 +1804,34 @@ wsfft_status_t wsfft_execute_batched(int count, const wsfft_plan_t* plans, const
     return batched(count, plans, in, out, adjoint, stream, false);
 }
 
+// One plan over `count` arrays back to back: the same launches as the call
+// above makes for such a batch, without lists of `count` entries to build and
+// check (about 60 ns of host time per array: 2.4 ms for 40000 short signals
+// whose transform takes 30 us).
+wsfft_status_t wsfft_execute_many(wsfft_plan_t plan, const void* in, void* out, int count, int adjoint,
+                                  hipStream_t stream) {
+    if (count < 0) return WSFFT_ERROR_INVALID_VALUE;
+    if (count == 0) return WSFFT_SUCCESS;
+    const wsfft_status_t st = check_exec(plan, in, out);
+    if (st != WSFFT_SUCCESS) return st;
+    if (uses_work(plan, in, out)) return WSFFT_ERROR_INVALID_VALUE;
+    const uintptr_t span = (uintptr_t)(plan->n[0] * plan->n[1] * plan->n[2] * elem_bytes(plan->dtype));
+    const uintptr_t i0 = (uintptr_t)in, o0 = (uintptr_t)out, all = span * (uintptr_t)count;
+    if (!plan->passes.empty() && (in == out || o0 >= i0 + all || i0 >= o0 + all)) {
+        for (size_t pi = 0; pi < plan->passes.size(); ++pi)
+            if (!launch_pass(plan, pi, in, out, adjoint ? 1 : 0, stream, count)) return WSFFT_ERROR_HIP;
+        return WSFFT_SUCCESS;
+    }
+    const std::vector<wsfft_plan_t> plans((size_t)count, plan);
+    std::vector<const void*> ins((size_t)count);
+    std::vector<void*> outs((size_t)count);
+    for (int i = 0; i < count; ++i) {
+        ins[i] = reinterpret_cast<const void*>(i0 + span * (uintptr_t)i);
+        outs[i] = reinterpret_cast<void*>(o0 + span * (uintptr_t)i);
+    }
+    return batched(count, plans.data(), ins.data(), outs.data(), adjoint, stream, false);
+}
+
 wsfft_status_t wsfft_tune_batched(int count, const wsfft_plan_t* plans, const void* const* in, void* const* out,
                                   int adjoint, hipStream_t stream) {
     const wsfft_status_t st = batched(count, plans, in, out, adjoint, stream, true);

@@ -212,3 +212,11 @@ def test_batch_spin_limit_rejects_invalid_plans(lib):
     f.argtypes = [ctypes.c_void_p, ctypes.c_uint]
     assert f(None, 5) == BADPLAN
     assert f(ctypes.c_void_p(0x1000), 5) == BADPLAN
+
+
+def test_execute_many_argument_checks(lib):
+    lib.wsfft_execute_many.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_int,
+                                       ctypes.c_void_p]
+    assert lib.wsfft_execute_many(None, None, None, -1, 0, None) == INVALID
+    assert lib.wsfft_execute_many(None, None, None, 0, 0, None) == 0
+    assert lib.wsfft_execute_many(None, 64, 64, 2, 0, None) == 8   # invalid plan

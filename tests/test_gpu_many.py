@@ -1,0 +1,50 @@
+"""One plan over arrays back to back (wsfft_execute_many) against
+wsfft_execute_batched over the same entries, bit for bit."""
+import pytest
+import torch
+
+from gpu_helpers import need_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ws():
+    return need_gpu()
+
+
+def bits(t):
+    return torch.view_as_real(t).view(torch.int32)
+
+
+@pytest.mark.parametrize("shape,count", [((256, 1, 1), 5), ((256, 1, 1), 1), ((27, 6, 1), 9), ((48, 36, 4), 3),
+                                         ((65536, 1, 1), 2), ((1, 1, 1), 4), ((512, 512, 96), 1)], ids=str)
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_many_matches_batched(ws, shape, count, adjoint, in_place):
+    nx, ny, nz = shape
+    g = torch.Generator(device="cuda").manual_seed(nx + count)
+    x = torch.view_as_complex(torch.randn((count, nz, ny, nx, 2), generator=g, device="cuda"))
+    p = ws.Plan(nx, ny, nz, "c64", -1)
+    want, got = x.clone(), x.clone()
+    src_w, src_g = (want, got) if in_place else (x, x)
+    if in_place and p.work_bytes:   # entries would share the plan's work buffer
+        for call in (lambda: ws.execute_many(p, got, got, count, adjoint),
+                     lambda: ws.execute_batched([p] * count, list(want), list(want), adjoint)):
+            with pytest.raises(ws.WsfftError) as e:
+                call()
+            assert e.value.status == 1
+        return
+    ws.execute_batched([p] * count, list(src_w), list(want), adjoint)
+    ws.execute_many(p, src_g, got, count, adjoint)
+    assert torch.equal(bits(want), bits(got))
+
+
+def test_many_of_no_arrays_and_of_16bit(ws):
+    p = ws.Plan(64, 1, 1, "fp16", -1)
+    e = torch.empty((0, 64, 2), dtype=torch.float16, device="cuda")
+    ws.execute_many(p, e, e.clone(), 0)
+    x = torch.randn((7, 64, 2), device="cuda").half()
+    y = ws.execute_many(p, x, torch.empty_like(x), 7)
+    z = torch.stack([p.execute(r.contiguous()) for r in x])
+    assert torch.equal(y.view(torch.int16), z.view(torch.int16))
