@@ -289,6 +289,10 @@ void wsfft_batch_plan_destroy(wsfft_batch_plan_t batch);
  * overwritten (its y and z passes run in place there); out: nx*ny*nz FP32.
  * wsfft_execute_c2r_inverse: the same times 1/(nx*ny*nz), so that
  * c2r_inverse(r2c(a)) = a.
+ * wsfft_execute_c2r_inverse_keep: the same as wsfft_execute_c2r_inverse, but
+ * `in` is only read: the y and z passes run in `work`, (nx/2+1)*ny*nz
+ * complex64 (half_pitch*ny*nz for padded rows), 8-byte aligned, overlapping
+ * neither `in` nor `out` (unused, and may be NULL, when ny = nz = 1).
  * `in` and `out` must not overlap (in == out returns
  * WSFFT_ERROR_INVALID_VALUE); wsfft_execute and the complex calls return
  * WSFFT_ERROR_INVALID_VALUE for a real plan, and the real calls for a complex
@@ -313,6 +317,8 @@ wsfft_plan_t wsfft_plan_create_real_ex(int64_t nx, int64_t ny, int64_t nz, unsig
 wsfft_status_t wsfft_execute_r2c(wsfft_plan_t plan, const float* in, void* out, hipStream_t stream);
 wsfft_status_t wsfft_execute_c2r(wsfft_plan_t plan, void* in, float* out, hipStream_t stream);
 wsfft_status_t wsfft_execute_c2r_inverse(wsfft_plan_t plan, void* in, float* out, hipStream_t stream);
+wsfft_status_t wsfft_execute_c2r_inverse_keep(wsfft_plan_t plan, const void* in, void* work, float* out,
+                                              hipStream_t stream);
 int wsfft_plan_is_real(wsfft_plan_t plan);
 
 /* S of the stored 2^-S scaling (0 for WSFFT_C64); -1 for an invalid plan. */

@@ -97,6 +97,7 @@ _plan_create_real_ex = _sig("wsfft_plan_create_real_ex", _vp, [_i64, _i64, _i64,
 _execute_r2c = _sig("wsfft_execute_r2c", _int, [_vp, _vp, _vp, _vp])
 _execute_c2r = _sig("wsfft_execute_c2r", _int, [_vp, _vp, _vp, _vp])
 _execute_c2r_inverse = _sig("wsfft_execute_c2r_inverse", _int, [_vp, _vp, _vp, _vp])
+_execute_c2r_inverse_keep = _sig("wsfft_execute_c2r_inverse_keep", _int, [_vp, _vp, _vp, _vp, _vp])
 _plan_is_real = _sig("wsfft_plan_is_real", _int, [_vp])
 
 
@@ -395,6 +396,15 @@ class RealPlan:
         _check(fn(self._h, X.data_ptr(), out.data_ptr(), _stream(stream)), "execute_c2r")
         return out
 
+    def _c2r_inverse_keep(self, X):
+        """``c2r(X, inverse=True)`` that leaves X as it is."""
+        self._check(X, torch.complex64, self.half_size, "input")
+        out = torch.empty(tuple(X.shape[:-1]) + (self.nx,), dtype=torch.float32, device=X.device)
+        work = torch.empty_like(X) if self.ny > 1 or self.nz > 1 else None
+        _check(_execute_c2r_inverse_keep(self._h, X.data_ptr(), work.data_ptr() if work is not None else None,
+                                         out.data_ptr(), _stream(None)), "execute_c2r")
+        return out
+
     def execute_pass(self, index: int, x, out, mode: int = 0, stream=None):
         """Only pass `index` of r2c (mode 0) or c2r (1; 2 with 1/N)."""
         _check(_execute_pass(self._h, int(index), int(mode), x.data_ptr(), out.data_ptr(), _stream(stream)),
@@ -459,7 +469,7 @@ def irfftn(X: torch.Tensor, nx: int) -> torch.Tensor:
     """The inverse of :func:`rfftn` (1/N included) for a real last axis of nx
     points; X is not modified."""
     xyz = (int(nx),) + _real_xyz(X.shape)[1:]
-    return _cached_real_plan(xyz, X.device).c2r(X.contiguous().clone(), inverse=True)
+    return _cached_real_plan(xyz, X.device)._c2r_inverse_keep(X.contiguous())
 
 
 def get_plan(x: torch.Tensor, sign: int = -1, flags: int = 0) -> Plan:

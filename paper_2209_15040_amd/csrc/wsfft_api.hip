@@ -1247,8 +1247,10 @@ wsfft_status_t check_real(const wsfft_plan_s* plan, const void* in, const void* 
 // Enqueue pass index `pi` of a plan; returns false on a launch error.  Real
 // plans: the R2C passes in mode 0, the C2R passes otherwise.
 // With zc > 0, only planes [z0, z0 + zc) of the x or y pass (a plane chunk).
+// With `keep`, the input is read by the first pass only and `keep` takes its
+// place from then on (C2R passes that leave their input as it is).
 bool launch_pass(const wsfft_plan_s* plan, size_t pi, const void* in, void* out, int mode,
-                 hipStream_t stream, int64_t batch = 1, int64_t z0 = 0, int64_t zc = 0) {
+                 hipStream_t stream, int64_t batch = 1, int64_t z0 = 0, int64_t zc = 0, void* keep = nullptr) {
     const Pass& P = (plan->real && mode != 0) ? plan->cpasses[pi] : plan->passes[pi];
     PassArgs a = P.args;
     const int sign = mode == 0 ? plan->sign : -plan->sign;
@@ -1277,6 +1279,8 @@ bool launch_pass(const wsfft_plan_s* plan, size_t pi, const void* in, void* out,
     const bool ip = in == out;
     a.src = static_cast<const char*>(sel(ip ? P.src_sel_ip : P.src_sel)) + in_off;
     a.dst = static_cast<char*>(sel(ip ? P.dst_sel_ip : P.dst_sel)) + out_off;
+    if (keep && P.src_sel == 0 && pi > 0) a.src = keep;
+    if (keep && P.dst_sel == 0) a.dst = keep;
     a.scale = mode == 2 ? P.inv_scale : P.pass_scale;
     return k->launch(a, nullptr, grid, stream) == hipSuccess;
 }
@@ -1737,6 +1741,25 @@ wsfft_status_t wsfft_execute_r2c(wsfft_plan_t plan, const float* in, void* out, 
     if (st != WSFFT_SUCCESS) return st;
     for (size_t i = 0; i < plan->passes.size(); ++i)
         if (!launch_pass(plan, i, in, out, 0, stream)) return WSFFT_ERROR_HIP;
+    return WSFFT_SUCCESS;
+}
+
+// C2R with the z and y passes in `work` (one half spectrum) instead of in
+// place on the input: the first of them reads the input, so leaving it as it
+// is costs no pass (a caller's copy of a 512^3 half spectrum took 270 us of
+// the 900 us call).  A plan with the x pass alone uses no work memory.
+wsfft_status_t wsfft_execute_c2r_inverse_keep(wsfft_plan_t plan, const void* in, void* work, float* out,
+                                              hipStream_t stream) {
+    const wsfft_status_t st = check_real(plan, in, out, 8, 4);
+    if (st != WSFFT_SUCCESS) return st;
+    const size_t np = plan->cpasses.size();
+    if (np > 1) {
+        if (!work) return WSFFT_ERROR_NULL_POINTER;
+        if ((uintptr_t)work % 8) return WSFFT_ERROR_MISALIGNED;
+        if (work == in || work == (void*)out) return WSFFT_ERROR_INVALID_VALUE;
+    }
+    for (size_t i = 0; i < np; ++i)
+        if (!launch_pass(plan, i, in, out, 2, stream, 1, 0, 0, np > 1 ? work : nullptr)) return WSFFT_ERROR_HIP;
     return WSFFT_SUCCESS;
 }
 

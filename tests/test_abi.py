@@ -220,3 +220,8 @@ def test_execute_many_argument_checks(lib):
     assert lib.wsfft_execute_many(None, None, None, -1, 0, None) == INVALID
     assert lib.wsfft_execute_many(None, None, None, 0, 0, None) == 0
     assert lib.wsfft_execute_many(None, 64, 64, 2, 0, None) == 8   # invalid plan
+
+
+def test_execute_c2r_inverse_keep_rejects_invalid_plans(lib):
+    lib.wsfft_execute_c2r_inverse_keep.argtypes = [ctypes.c_void_p] * 5
+    assert lib.wsfft_execute_c2r_inverse_keep(None, 64, 128, 256, None) == 8

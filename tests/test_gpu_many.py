@@ -1,5 +1,6 @@
 """One plan over arrays back to back (wsfft_execute_many) against
-wsfft_execute_batched over the same entries, bit for bit."""
+wsfft_execute_batched over the same entries, bit for bit, and the C2R call that
+keeps its input against the one that overwrites it."""
 import pytest
 import torch
 
@@ -48,3 +49,30 @@ def test_many_of_no_arrays_and_of_16bit(ws):
     y = ws.execute_many(p, x, torch.empty_like(x), 7)
     z = torch.stack([p.execute(r.contiguous()) for r in x])
     assert torch.equal(y.view(torch.int16), z.view(torch.int16))
+
+
+# one axis, two, three; a split y or z axis; unaligned rows
+@pytest.mark.parametrize("shape", [(512, 1, 1), (36, 27, 1), (64, 1, 96), (48, 36, 32), (8, 2048, 6), (16, 3, 2048),
+                                   (4, 2048, 2048)], ids=str)
+def test_c2r_keep(ws, shape):
+    nx, ny, nz = shape
+    g = torch.Generator(device="cuda").manual_seed(nx)
+    X = torch.view_as_complex(torch.randn((nz, ny, nx // 2 + 1, 2), generator=g, device="cuda"))
+    before = X.clone()
+    got = ws.irfftn(X, nx)
+    assert torch.equal(bits(X), bits(before))
+    want = ws.RealPlan(nx, ny, nz).c2r(X.clone(), inverse=True)
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+
+
+def test_c2r_keep_argument_checks(ws):
+    p = ws.RealPlan(8, 4, 2)
+    buf = torch.zeros(4096, dtype=torch.float32, device="cuda")
+    a = buf.data_ptr()
+    call = ws._execute_c2r_inverse_keep
+    assert call(p.handle, a, None, a + 8192, None) == 3
+    assert call(p.handle, a, a, a + 8192, None) == 1
+    assert call(p.handle, a, a + 8192, a + 8192, None) == 1
+    assert call(p.handle, a, a + 4, a + 8192, None) == 4
+    assert call(p.handle, None, a, a + 8192, None) == 3
+    assert call(ws.Plan(8, 4, 2).handle, a, a + 4096, a + 8192, None) == 1
