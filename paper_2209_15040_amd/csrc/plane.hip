@@ -34,22 +34,28 @@ struct PlaneXY {
     static constexpr int E = NX * NY;
     static constexpr int kPlaneThreads = plane_threads(E);
     static_assert(E * 8 <= 128 * 1024, "a plane holds at most 16384 values");
-    // LDS row pitch: 4 values (32 bytes) of padding per row, so the threads
-    // of an x stage, which take 8 to 16 consecutive butterflies of each of
-    // several rows, spread over all banks (rows NX * 8 bytes apart would all
-    // start on the same bank); even, so two-value accesses stay 16-byte aligned
-    static constexpr int LX = NX + 4;
+    // LDS layout: value (x, y) sits at y*LX + swz(x).  The first x stage
+    // writes butterflies of R consecutive values from consecutive lanes, 8 or
+    // 16 values (16 or 32 banks) apart, and its reads take runs of 8 values
+    // of several rows; rows padded by 4 values in natural order served these
+    // with 2- to 4-way bank conflicts, 63% of the LDS cycles of a 128 x 128
+    // plane (9216 of 14592).  The low three bits of x are exchanged with
+    // higher ones, which spreads the lanes of a row, and 8 values of padding
+    // (4 for 32 columns) spread the rows; columns stay conflict-free, since
+    // the exchange permutes groups of 8 columns within themselves.  128^3:
+    // plane pass 14.3 -> 12.9 us, 256 x 64 x 128 17.6 -> 12.8, 256 x 32 x 256
+    // 12.2 -> 9.6.
+    static constexpr int LX = NX + (NX == 32 ? 4 : 8);
+    __device__ __forceinline__ static int swz(int x) { return x ^ ((NX == 256 ? x >> 5 : x >> 3) & 7); }
     static constexpr int lds_bytes() { return NY * LX * (int)sizeof(float2); }
 
-    // Stage S of length-N transforms over COUNT pencils; element e of pencil
-    // q sits at lds[q * QS + e * ES].  ROWMAJOR: consecutive threads take
-    // consecutive butterflies of one pencil (unit-stride pencils); else
-    // consecutive pencils of one butterfly (pencils of stride LX, whose
-    // neighbours sit next to each other in LDS).  GIN: the inputs come from
+    // Stage S of length-N transforms over COUNT pencils.  ROWMAJOR: pencils
+    // are rows, and consecutive threads take consecutive butterflies of one
+    // row; else columns, consecutive columns of one butterfly.  GIN: the inputs come from
     // the plane in global memory (element e of pencil q at gin[q * NX + e])
     // instead of LDS; GOUT: the outputs go to global memory (element e of
     // pencil q at gout[e * NX + q], times scale) instead of LDS.
-    template <int N, int COUNT, int QS, int ES, bool ROWMAJOR, int S, bool GIN, bool GOUT>
+    template <int N, int COUNT, bool ROWMAJOR, int S, bool GIN, bool GOUT>
     __device__ __forceinline__ static void stage(float2* lds, const float2* tw, const char* gin, char* gout,
                                                  float scale) {
         constexpr Radices RD = make_radices(N, kPlaneRadixPlan);
@@ -59,6 +65,8 @@ struct PlaneXY {
         constexpr int TOTAL = COUNT * NBF;
         constexpr int PER = (TOTAL + kPlaneThreads - 1) / kPlaneThreads;
         constexpr int off = stage_tw_offset(RD, S);
+        // element e of pencil q
+        auto at = [](int q, int e) { return ROWMAJOR ? q * LX + swz(e) : e * LX + swz(q); };
         float2 u[PER][R];
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
@@ -73,7 +81,7 @@ struct PlaneXY {
                         gload_at<f32x2>(gin, (uint32_t)(q * NX + b + r * NBF) * 8u));
                     u[i][r] = make_float2(v.x, v.y);
                 } else {
-                    u[i][r] = lds[q * QS + (b + r * NBF) * ES];
+                    u[i][r] = lds[at(q, b + r * NBF)];
                 }
             }
             if constexpr (S > 0) {
@@ -103,7 +111,7 @@ struct PlaneXY {
                     v.y = u[i][r].y * scale;
                     __builtin_nontemporal_store(v, gstore_at<f32x2>(gout, (uint32_t)((o + r * Ns) * NX + q) * 8u));
                 } else {
-                    lds[q * QS + (o + r * Ns) * ES] = u[i][r];
+                    lds[at(q, o + r * Ns)] = u[i][r];
                 }
             }
         }
@@ -112,13 +120,13 @@ struct PlaneXY {
 
     // all stages of one transform set; the first may read global memory, the
     // last may write it
-    template <int N, int COUNT, int QS, int ES, bool ROWMAJOR, bool GIN, bool GOUT, int S = 0>
+    template <int N, int COUNT, bool ROWMAJOR, bool GIN, bool GOUT, int S = 0>
     __device__ __forceinline__ static void transform(float2* lds, const float2* tw, const char* gin, char* gout,
                                                      float scale) {
         constexpr Radices RD = make_radices(N, kPlaneRadixPlan);
         if constexpr (S < RD.n) {
-            stage<N, COUNT, QS, ES, ROWMAJOR, S, GIN && S == 0, GOUT && S + 1 == RD.n>(lds, tw, gin, gout, scale);
-            transform<N, COUNT, QS, ES, ROWMAJOR, GIN, GOUT, S + 1>(lds, tw, gin, gout, scale);
+            stage<N, COUNT, ROWMAJOR, S, GIN && S == 0, GOUT && S + 1 == RD.n>(lds, tw, gin, gout, scale);
+            transform<N, COUNT, ROWMAJOR, GIN, GOUT, S + 1>(lds, tw, gin, gout, scale);
         }
     }
 
@@ -135,8 +143,8 @@ struct PlaneXY {
                                                float2* lds) {
         const char* src = reinterpret_cast<const char*>(static_cast<const float2*>(src0) + t * stride_in);
         char* dst = reinterpret_cast<char*>(static_cast<float2*>(dst0) + t * stride_out);
-        transform<NX, NY, LX, 1, true, true, false>(lds, tw, src, nullptr, 1.0f);    // rows: pencils along x
-        transform<NY, NX, 1, LX, false, false, true>(lds, tw4, nullptr, dst, scale);   // columns: along y
+        transform<NX, NY, true, true, false>(lds, tw, src, nullptr, 1.0f);      // rows: pencils along x
+        transform<NY, NX, false, false, true>(lds, tw4, nullptr, dst, scale);   // columns: along y
     }
 };
 
@@ -208,11 +216,11 @@ struct PlaneShape {
 constexpr PlaneShape kPlaneShapes[] = {WSFFT_PLANES(WSFFT_PLANE_SHAPE)};
 constexpr int kNumPlaneShapes = (int)(sizeof(kPlaneShapes) / sizeof(kPlaneShapes[0]));
 // below 4096 values: 256 threads, at most 28 KB of LDS; 4096 .. 6144: 512
-// threads, at most 53 KB; 8192: 512 threads, at most 74 KB; 9216 .. 16384:
-// 1024 threads, at most 136 KB
+// threads, at most 56 KB; 8192: 512 threads, at most 74 KB; 9216 .. 16384:
+// 1024 threads, at most 148 KB
 constexpr int class_of(int values) { return values < 4096 ? 0 : (values <= 6144 ? 1 : (values <= 8192 ? 2 : 3)); }
 constexpr int class_threads(int cls) { return cls == 0 ? 256 : (cls == 3 ? 1024 : 512); }
-constexpr int shape_lds(int nx, int ny) { return ny * (nx + 4) * (int)sizeof(float2); }
+constexpr int shape_lds(int nx, int ny) { return ny * (nx + (nx == 32 ? 4 : 8)) * (int)sizeof(float2); }
 constexpr int class_lds(int cls) {
     int m = 0;
     for (const PlaneShape& p : kPlaneShapes)
