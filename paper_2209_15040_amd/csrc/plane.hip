@@ -167,16 +167,33 @@ __global__ __launch_bounds__(plane_threads(NX * NY)) void plane_kernel(PassArgs 
     PlaneXY<NX, NY, SIGN>::run_plane(a, t, lds_dyn);
 }
 
+// One array, with 64 bytes of arguments (SmallArgs).
+template <int NX, int NY, int SIGN>
+__global__ __launch_bounds__(plane_threads(NX * NY)) void plane_single_kernel(SmallArgs a) {
+    extern __shared__ float2 lds_dyn[];
+    PlaneXY<NX, NY, SIGN>::run(a.src, a.dst, a.tw, a.tw4, a.os1_in, a.os1_out, a.scale, blockIdx.x, lds_dyn);
+}
+
 template <int NX, int NY, int SIGN>
 hipError_t plane_launch(const PassArgs& a, const BatchTable* bt, dim3 grid, hipStream_t s) {
     static const BatchTable kNone{};
     constexpr int lds = PlaneXY<NX, NY, SIGN>::lds_bytes();
+    if (!bt && SmallArgs::fits(a)) {
+        hipLaunchKernelGGL((plane_single_kernel<NX, NY, SIGN>), grid, dim3(plane_threads(NX * NY)), lds, s, SmallArgs(a));
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL((plane_kernel<NX, NY, SIGN>), grid, dim3(plane_threads(NX * NY)), lds, s, a, bt ? *bt : kNone);
     return hipGetLastError();
 }
 
 template <int NX, int NY, int SIGN>
 hipError_t plane_prepare() {
+    if constexpr (PlaneXY<NX, NY, SIGN>::lds_bytes() > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&plane_single_kernel<NX, NY, SIGN>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 PlaneXY<NX, NY, SIGN>::lds_bytes());
+        if (e != hipSuccess) return e;
+    }
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&plane_kernel<NX, NY, SIGN>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, PlaneXY<NX, NY, SIGN>::lds_bytes());
 }

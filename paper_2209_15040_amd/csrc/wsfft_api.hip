@@ -1625,9 +1625,11 @@ static wsfft_status_t poisson_real(const wsfft_plan_s* plan, const float* f, flo
         a.dst = dst;
         a.scale = scale;
         a.tw = plan->tw_dev + P.tw_off + (int64_t)k->plan * P.n;   // the stage tables of k's radix plan
-        a.sym_nx = (int32_t)nxh;
-        a.sym_ny = (int32_t)ny;
-        a.sym_half = 1;
+        if (k->fused == kFusedSolveZ) {
+            a.sym_nx = (int32_t)nxh;
+            a.sym_ny = (int32_t)ny;
+            a.sym_half = 1;
+        }
         return k->launch(a, nullptr, dim3((unsigned)blocks_for(P, k)), stream) == hipSuccess;
     };
     const double N = (double)nx * (double)ny * (double)nz;
@@ -1667,8 +1669,10 @@ wsfft_status_t wsfft_poisson_solve(wsfft_plan_t plan, const float* f, float* u, 
         a.dst = dst;
         a.scale = scale;
         a.tw = plan->tw_dev + P.tw_off + (int64_t)k->plan * P.n;   // the stage tables of k's radix plan
-        a.sym_nx = (int32_t)nx;
-        a.sym_ny = (int32_t)ny;
+        if (k->fused == kFusedPoisson) {
+            a.sym_nx = (int32_t)nx;
+            a.sym_ny = (int32_t)ny;
+        }
         return k->launch(a, nullptr, dim3((unsigned)blocks_for(P, k)), stream) == hipSuccess;
     };
     const double N = (double)nx * (double)ny * (double)nz;
