@@ -206,7 +206,7 @@ constexpr StridedGeo cfg_strided(int N, int bytes, int vb) {
 // 4237 -> 5899, 216 3898 -> 5919, 243 3782 -> 5418, 288 4440 -> 5781, 324
 // 4617 -> 5829, 384 4845 -> 5796, 432 3950 -> 5253, 486 3939 -> 5562, 512
 // 5792 -> 6104, 576 5281 -> 5790, 648 4048 -> 5616, 768 4548 -> 5889, 864
-// 3911 -> 5404, 972 3891 -> 5020, 4096 5361 -> 5853, 7776 2709 -> 4361.  The
+// 3911 -> 5404, 972 3891 -> 5020, 4096 5361 -> 5853, 7776 2709 -> 4698, 8192 4714 -> 4925, 15552 3496 -> 3820.  The
 // FP16-arithmetic entries never have more stages than the rule's schedule
 // (each stage rounds to FP16).
 struct ContigGeo {
@@ -226,8 +226,9 @@ constexpr ContigGeo kContig8[] = {   // complex64
     {768, 32, 2, 1, false},  {864, 32, 4, 0, false},  {972, 81, 3, 2, true},   {1296, 108, 4, 2, false},
     {1458, 81, 3, 0, true},  {1728, 96, 2, 2, false}, {1944, 122, 1, 1, true}, {2187, 243, 2, 1, true},
     {2304, 192, 1, 2, false}, {2592, 144, 1, 0, true}, {2916, 162, 1, 0, true}, {3456, 192, 1, 1, false},
-    {3888, 486, 1, 1, true}, {4096, 256, 1, 2, false}, {4374, 244, 1, 1, false}, {4608, 288, 1, 1, false},
-    {6561, 729, 1, 1, false}, {7776, 432, 1, 0, false}, {8748, 365, 1, 0, false}};
+    {3888, 486, 1, 1, true}, {4096, 256, 1, 2, false}, {4374, 486, 1, 1, false}, {4608, 288, 1, 1, false},
+    {5184, 192, 1, 1, false}, {6561, 729, 1, 1, false}, {7776, 648, 1, 2, false}, {8192, 512, 1, 0, false},
+    {8748, 972, 1, 1, false}, {9216, 256, 1, 1, false}, {12288, 384, 1, 1, false}, {15552, 648, 1, 0, false}};
 constexpr ContigGeo kContig4[] = {   // 4-byte storage, FP32 values
     {2, 1, 256, 0, true},    {3, 1, 256, 0, true},    {6, 1, 64, 0, true},     {8, 1, 64, 0, true},
     {9, 1, 64, 0, true},     {12, 1, 64, 0, true},    {16, 1, 64, 0, true},    {18, 3, 42, 1, true},
@@ -250,6 +251,16 @@ constexpr ContigGeo kContig4m[] = {   // 4-byte storage, FP16 values
     {384, 16, 4, 1, false},  {432, 24, 5, 0, true},   {486, 27, 18, 1, true},  {648, 36, 7, 1, true},
     {729, 27, 9, 0, false},  {768, 32, 2, 1, false},  {864, 32, 2, 0, false},  {1024, 32, 8, 0, false},
     {2048, 64, 1, 0, false}};
+
+// Exchange rounds of the default contiguous complex64 kernel: two for the long
+// pencils whose LDS then lets two or three workgroups share a CU instead of
+// one or two (GB/s at 1 GiB, one round -> two: 5184 4601 -> 5415, 9216 4828 ->
+// 5461, 10368 3755 -> 4508, 11664 3640 -> 4083, 12288 3788 -> 4396, 13122 3600
+// -> 3969).  The half-spectrum passes need their whole pencil in LDS and keep
+// the rules' geometry at these lengths.
+constexpr int cfg_K_contig(int N, int bytes) {
+    return bytes == 8 && (N == 5184 || N == 9216 || N == 10368 || N == 11664 || N == 12288 || N == 13122) ? 2 : 1;
+}
 
 // Geometry of the default contiguous kernel: the measured entry, else the rules.
 constexpr ContigGeo cfg_contig(int N, int bytes, int vb) {

@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
 
 LENGTHS = [2, 3, 4, 6, 8, 9, 12, 16, 18, 24, 27, 32, 36, 48, 54, 64, 72, 81, 96, 108, 128, 144, 162, 192, 216, 243, 256,
            288, 324, 384, 432, 486, 512, 576, 648, 729, 768, 864, 972, 1024, 1296, 1458, 1728, 1944, 2048, 2187, 2304,
-           2592, 2916, 3456, 3888, 4096, 4374, 4608, 6561, 7776, 8748]
+           2592, 2916, 3456, 3888, 4096, 4374, 4608, 5184, 6561, 7776, 8192, 8748, 9216, 10368, 11664,
+           12288, 13122, 15552]
 
 
 @pytest.fixture(scope="module")
@@ -66,7 +67,7 @@ def test_16bit(ws, n, kind, flags):
             assert e <= (3.0 * floor if kind == "bf16" else 3e-3), (n, rows, off, e, floor, p.describe())
 
 
-@pytest.mark.parametrize("n", [m for m in LENGTHS if m <= 1458])
+@pytest.mark.parametrize("n", [m for m in LENGTHS if m <= 1458 or m in (5184, 8192, 9216, 12288, 13122)])
 def test_real(ws, n):
     nx = 2 * n
     for rows, pitch in ((1, 0), (36, 0), (18, (n + 1 + 15) // 16 * 16), (6, n + 4)):
