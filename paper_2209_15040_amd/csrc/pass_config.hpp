@@ -172,6 +172,12 @@ constexpr int cfg_K_four_step(int N, int P, int K, int vb) {
     return K;
 }
 
+// Exchange rounds of the strided kernel that streams past the caches: 256
+// points of complex64 take one (second pass of 65536 x 1024: 184.7 us, two
+// rounds 194.5; y axis of 512x256x512: 186.8 and 194.1), where the cached and
+// fused kernels of smaller arrays take the two of the table.
+constexpr int cfg_K_stream(int N, int bytes, int K) { return N == 256 && bytes == 8 ? 1 : K; }
+
 // Geometry of the default strided kernel: the measured entry, else the rules.
 constexpr StridedGeo cfg_strided(int N, int bytes, int vb) {
     if (bytes == 8) {
