@@ -469,7 +469,9 @@ def irfftn(X: torch.Tensor, nx: int) -> torch.Tensor:
     """The inverse of :func:`rfftn` (1/N included) for a real last axis of nx
     points; X is not modified."""
     xyz = (int(nx),) + _real_xyz(X.shape)[1:]
-    return _cached_real_plan(xyz, X.device)._c2r_inverse_keep(X.contiguous())
+    # a pending conjugation or negation lives in the tensor, not in its memory,
+    # and contiguous() keeps it pending
+    return _cached_real_plan(xyz, X.device)._c2r_inverse_keep(X.resolve_conj().resolve_neg().contiguous())
 
 
 def get_plan(x: torch.Tensor, sign: int = -1, flags: int = 0) -> Plan:
