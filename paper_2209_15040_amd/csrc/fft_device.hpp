@@ -1071,16 +1071,26 @@ struct PencilPass {
             }
             return;
         }
+        // Padded or unaligned rows, element by element; every load is issued
+        // before the first LDS write (C2R x pass of 512^3 with rows of 272: 198
+        // us; waiting after each four loads 305, unstaged 201.  16-byte loads
+        // of rows with an even pitch gained 6 us there and cost the packed rows
+        // above 6 us).
         constexpr int PER = (TOT + TH - 1) / TH;
         const uint32_t pitch = (uint32_t)a.os1_in;
-#pragma unroll 4
+        SW buf[PER];
+#pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int idx = (int)threadIdx.x + i * TH;
             if (idx >= lim) continue;
-            const int p = idx / W, e = idx % W;
-            const uint32_t at = ((uint32_t)p * pitch + (uint32_t)e) * IO::bytes;
-            if constexpr (IO::bytes == 8) lds[lidx(p, e)] = IO::template ld<NT>(base, at);
-            else lds[lidx(p, e)] = NT ? __builtin_nontemporal_load(gload_at<SW>(base, at)) : *gload_at<SW>(base, at);
+            const uint32_t at = ((uint32_t)(idx / W) * pitch + (uint32_t)(idx % W)) * IO::bytes;
+            if constexpr (IO::bytes == 8) buf[i] = IO::template ld<NT>(base, at);
+            else buf[i] = NT ? __builtin_nontemporal_load(gload_at<SW>(base, at)) : *gload_at<SW>(base, at);
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int idx = (int)threadIdx.x + i * TH;
+            if (idx < lim) lds[lidx(idx / W, idx % W)] = buf[i];
         }
     }
     template <int W>
