@@ -130,11 +130,16 @@ constexpr int cfg_K_strided(int N, int bytes, int plan = 0, int vb = 8) {
 // MiB; an entry is the best of the four together and stands where it gains 2%
 // or more.  GB/s (y / z, 256 MiB complex64), rule -> entry: 162 4806/4433 ->
 // 5688/4979, 216 4769/4514 -> 5313/5062, 243 4710/4519 -> 5161/4972, 288
-// 4926/4576 -> 5512/5052, 324 4621/4369 -> 5458/4943, 432 3188/3013 ->
-// 4733/4609, 486 3120/3050 -> 4700/4521, 576 3673/3465 -> 5017/4527, 648
+// 4926/4576 -> 5512/5052, 324 4680/4404 -> 4896/4497, 432 3188/3013 ->
+// 4733/4609, 486 3120/3050 -> 4700/4521, 576 3673/3465 -> 4914/4460, 648
 // 3440/3348 -> 4742/4682, 729 3545/3403 -> 4593/4560, 768 3861/3685 ->
-// 4915/4764, 864 2799/2713 -> 4745/4700, 972 2581/2538 -> 4167/4170, 1024
-// 4686/3630 -> 5047/3855.  256 points keep the rule's tile with the exchange
+// 4915/4764, 864 2799/2713 -> 4407/4084, 972 2581/2538 -> 4167/4170, 1024
+// 4686/3630 -> 5047/3855.  No complex64 entry rounds more than the rule's
+// radix schedule: the relative error of single passes against FP64 (2^21 values
+// per length, 0.2% between seeds) grew by 3.4% at 576 points in four stages
+// instead of three, 2.4% at 864 in 27 x 32 and 2.1% at 324 in 18 x 18, so these
+// keep the rule's radices (5019/4481, 4781/4348 and 5510/4968 GB/s without that
+// condition).  256 points keep the rule's tile with the exchange
 // in two rounds, four workgroups per CU instead of two: 5499/5142 ->
 // 5436/5145 at 256 MiB, 5071/4802 -> 5512/5317 at 64.  (Complex64 tiles of
 // 128 and 256 points in 64 columns gained 4-7% there but leave the chip short
@@ -147,9 +152,9 @@ struct StridedGeo {
 };
 constexpr StridedGeo kStrided8[] = {   // complex64
     {72, 9, 32, 1, 0},   {81, 9, 32, 1, 0},   {162, 9, 32, 1, 0},  {216, 6, 32, 2, 0},
-    {243, 9, 32, 3, 0},  {256, 8, 32, 2, 1},  {288, 18, 32, 1, 0}, {324, 18, 32, 2, 0},
-    {432, 12, 16, 2, 1}, {486, 27, 16, 2, 1}, {576, 16, 16, 2, 2}, {648, 27, 16, 2, 0}, {729, 27, 16, 3, 0},
-    {768, 32, 16, 3, 1}, {864, 32, 16, 2, 0}, {972, 27, 16, 2, 0}, {1024, 32, 16, 2, 0}};
+    {243, 9, 32, 3, 0},  {256, 8, 32, 2, 1},  {288, 18, 32, 1, 0}, {324, 12, 16, 2, 1},
+    {432, 12, 16, 2, 1}, {486, 27, 16, 2, 1}, {576, 16, 16, 3, 1}, {648, 27, 16, 2, 0}, {729, 27, 16, 3, 0},
+    {768, 32, 16, 3, 1}, {864, 24, 16, 3, 1}, {972, 27, 16, 2, 0}, {1024, 32, 16, 2, 0}};
 constexpr StridedGeo kStrided4[] = {   // 4-byte storage, FP32 values
     {48, 8, 32, 1, 0},   {64, 8, 64, 1, 0},   {72, 9, 32, 1, 0},   {81, 9, 64, 1, 0},
     {96, 4, 64, 2, 0},   {108, 12, 32, 1, 0},  {128, 8, 64, 2, 0},  {144, 12, 64, 1, 0},  {162, 9, 64, 2, 0},
@@ -208,33 +213,37 @@ constexpr StridedGeo cfg_strided(int N, int bytes, int vb) {
 // short and radix-3 lengths, direct from about 500 points on where pencils
 // are whole lines.  GB/s at 256 MiB of complex64, rule -> entry: 16 3236 ->
 // 6281, 27 1191 -> 5823, 32 3546 -> 6235, 36 1290 -> 5849, 64 5903 -> 6183,
-// 81 1296 -> 5880, 96 5299 -> 6096, 108 1175 -> 5718, 144 1908 -> 6034, 192
+// 81 1296 -> 5880, 96 5299 -> 6096, 108 1175 -> 5870, 144 1908 -> 6034, 192
 // 4237 -> 5899, 216 3898 -> 5919, 243 3782 -> 5418, 288 4440 -> 5781, 324
-// 4617 -> 5829, 384 4845 -> 5796, 432 3950 -> 5253, 486 3939 -> 5562, 512
-// 5792 -> 6104, 576 5281 -> 5790, 648 4048 -> 5616, 768 4548 -> 5889, 864
-// 3911 -> 5404, 972 3891 -> 5020, 4096 5361 -> 5853, 7776 2709 -> 4698, 8192 4714 -> 4925, 15552 3496 -> 3820.  The
-// FP16-arithmetic entries never have more stages than the rule's schedule
-// (each stage rounds to FP16).
+// 4617 -> 5829, 384 4845 -> 5796, 432 3950 -> 5253, 486 3939 -> 5392, 512
+// 5792 -> 6104, 576 5281 -> 5902, 648 4048 -> 5305, 768 4548 -> 5889, 864
+// 3911 -> 5404, 972 3891 -> 5459, 1296 4174 -> 5744, 1728 4014 -> 5628, 4096
+// 5361 -> 5853, 7776 2704 -> 4073, 8192 4714 -> 4925, 15552 3496 -> 3820.  As
+// in the strided table, no entry rounds more than the rule's radix schedule:
+// more or narrower stages raised the error by 6.1% at 576 points, 5.6% at 1296,
+// 4.8% at 1728, 4.2% at 108, 0.5-2.1% at 486, 648, 729, 972, 2187, 3888, 4374,
+// 6561, 7776 and 8748 (FP16 arithmetic: 1.2% at 729), which keep the rule's
+// radices; 2187, 3888, 4374 and 8748 then have no better geometry than the
+// rule's.
 struct ContigGeo {
     int n, T, P, plan;
     bool stage;
 };
 constexpr ContigGeo kContig8[] = {   // complex64
-    {2, 1, 256, 0, true},    {3, 1, 256, 0, true},    {4, 1, 128, 0, true},    {6, 1, 128, 0, true},
-    {8, 1, 256, 0, true},    {9, 1, 256, 0, true},    {12, 1, 64, 2, true},    {16, 1, 64, 2, true},
-    {18, 2, 64, 1, true},    {24, 2, 32, 1, true},    {27, 1, 128, 0, true},   {32, 2, 64, 1, true},
-    {36, 3, 42, 0, true},    {48, 2, 32, 0, true},    {54, 6, 21, 0, true},    {64, 4, 32, 0, true},
-    {72, 9, 28, 0, true},    {81, 9, 28, 0, true},    {96, 8, 16, 0, true},    {108, 9, 14, 2, true},
-    {128, 8, 16, 0, true},   {144, 12, 10, 0, true},  {162, 27, 9, 2, true},   {192, 16, 8, 0, true},
-    {216, 12, 10, 0, true},  {243, 27, 18, 1, true},  {256, 16, 16, 0, true},  {288, 16, 16, 0, true},
-    {324, 18, 14, 0, true},  {384, 16, 4, 0, true},   {432, 24, 5, 0, true},   {486, 54, 9, 1, true},
-    {512, 32, 4, 1, false},  {576, 48, 5, 2, true},   {648, 36, 7, 1, true},   {729, 81, 6, 1, true},
-    {768, 32, 2, 1, false},  {864, 32, 4, 0, false},  {972, 81, 3, 2, true},   {1296, 108, 4, 2, false},
-    {1458, 81, 3, 0, true},  {1728, 96, 2, 2, false}, {1944, 122, 1, 1, true}, {2187, 243, 2, 1, true},
+    {2, 1, 256, 0, true}, {3, 1, 256, 0, true}, {4, 1, 128, 0, true}, {6, 1, 128, 0, true}, {8, 1, 256, 0, true},
+    {9, 1, 256, 0, true}, {12, 1, 64, 2, true}, {16, 1, 64, 2, true}, {18, 2, 64, 1, true}, {24, 2, 32, 1, true},
+    {27, 1, 128, 0, true}, {32, 2, 64, 1, true}, {36, 3, 42, 0, true}, {48, 2, 32, 0, true},
+    {54, 6, 21, 0, true}, {64, 4, 32, 0, true}, {72, 9, 28, 0, true}, {81, 9, 28, 0, true}, {96, 8, 16, 0, true},
+    {108, 9, 14, 0, true}, {128, 8, 16, 0, true}, {144, 12, 10, 0, true}, {162, 27, 9, 2, true},
+    {192, 16, 8, 0, true}, {216, 12, 10, 0, true}, {243, 27, 18, 1, true}, {256, 16, 16, 0, true},
+    {288, 16, 16, 0, true}, {324, 18, 14, 0, true}, {384, 16, 4, 0, true}, {432, 24, 5, 0, true},
+    {486, 18, 7, 0, true}, {512, 32, 4, 1, false}, {576, 24, 10, 0, true}, {648, 24, 5, 0, true},
+    {729, 27, 4, 0, true}, {768, 32, 2, 1, false}, {864, 32, 4, 0, false}, {972, 81, 3, 0, true},
+    {1296, 108, 2, 0, true}, {1458, 81, 3, 0, true}, {1728, 72, 3, 0, false}, {1944, 122, 1, 1, true},
     {2304, 192, 1, 2, false}, {2592, 144, 1, 0, true}, {2916, 162, 1, 0, true}, {3456, 192, 1, 1, false},
-    {3888, 486, 1, 1, true}, {4096, 256, 1, 2, false}, {4374, 486, 1, 1, false}, {4608, 288, 1, 1, false},
-    {5184, 192, 1, 1, false}, {6561, 729, 1, 1, false}, {7776, 648, 1, 2, false}, {8192, 512, 1, 0, false},
-    {8748, 972, 1, 1, false}, {9216, 256, 1, 1, false}, {12288, 384, 1, 1, false}, {15552, 648, 1, 0, false}};
+    {4096, 256, 1, 2, false}, {4608, 288, 1, 1, false}, {5184, 192, 1, 1, false}, {6561, 243, 1, 0, false},
+    {7776, 216, 1, 0, false}, {8192, 512, 1, 0, false}, {9216, 256, 1, 1, false}, {12288, 384, 1, 1, false},
+    {15552, 648, 1, 0, false}};
 constexpr ContigGeo kContig4[] = {   // 4-byte storage, FP32 values
     {2, 1, 256, 0, true},    {3, 1, 256, 0, true},    {6, 1, 64, 0, true},     {8, 1, 64, 0, true},
     {9, 1, 64, 0, true},     {12, 1, 64, 0, true},    {16, 1, 64, 0, true},    {18, 3, 42, 1, true},
@@ -255,16 +264,17 @@ constexpr ContigGeo kContig4m[] = {   // 4-byte storage, FP16 values
     {144, 12, 10, 0, true},  {162, 9, 14, 0, true},   {192, 16, 8, 0, true},   {216, 12, 10, 0, true},
     {243, 9, 28, 0, true},   {256, 16, 16, 0, true},  {288, 18, 7, 0, true},   {324, 18, 7, 0, true},
     {384, 16, 4, 1, false},  {432, 24, 5, 0, true},   {486, 27, 18, 1, true},  {648, 36, 7, 1, true},
-    {729, 27, 9, 0, false},  {768, 32, 2, 1, false},  {864, 32, 2, 0, false},  {1024, 32, 8, 0, false},
+    {729, 81, 3, 1, false},  {768, 32, 2, 1, false},  {864, 32, 2, 0, false},  {1024, 32, 8, 0, false},
     {2048, 64, 1, 0, false}};
 
 // Exchange rounds of the default contiguous complex64 kernel: two for the long
 // pencils whose LDS then lets two or three workgroups share a CU instead of
 // one or two (GB/s at 1 GiB, one round -> two: 5184 4601 -> 5415, 9216 4828 ->
 // 5461, 10368 3755 -> 4508, 11664 3640 -> 4083, 12288 3788 -> 4396, 13122 3600
-// -> 3969).  The half-spectrum passes need their whole pencil in LDS and keep
+// -> 3969; 6561, an odd length, three: 4158 -> 4517).  The half-spectrum passes need their whole pencil in LDS and keep
 // the rules' geometry at these lengths.
 constexpr int cfg_K_contig(int N, int bytes) {
+    if (bytes == 8 && N == 6561) return 3;
     return bytes == 8 && (N == 5184 || N == 9216 || N == 10368 || N == 11664 || N == 12288 || N == 13122) ? 2 : 1;
 }
 
