@@ -1438,6 +1438,32 @@ bool launch_level_merged(int count, const wsfft_plan_t* plans, const void* const
                     return false;
             }
         }
+    // Arrays of one pass length whose rows are whole cache lines and those
+    // whose rows are not run different kernels (apply_row_policy): same tiles,
+    // other cache policy.  Few aligned bytes join the others' launch: 40 arrays
+    // of 24 .. 96 points per axis take 263 us apart and 222 together (FP16 229
+    // and 173), FP16 128 x 128 x 64 beside 81 x 81 x 64, 16 MiB of them aligned,
+    // 51 apart and 60 together.
+    constexpr int64_t kJoinBytes = int64_t(8) << 20;
+    for (size_t g = 0; g < groups.size();) {
+        size_t h = groups.size();
+        if (groups[g].k0->fused == kFusedNone && groups[g].k0->strided) {
+            int64_t bytes = 0;
+            for (int i : groups[g].idx)
+                bytes += plans[i]->n[0] * plans[i]->n[1] * plans[i]->n[2] * elem_bytes(plans[i]->dtype);
+            for (size_t q = 0; q < groups.size() && bytes <= kJoinBytes; ++q)
+                if (groups[q].k0->fused == kFusedCached && groups[q].k0->n == groups[g].k0->n && groups[q].k0->strided &&
+                    groups[q].kind == groups[g].kind && groups[q].sign == groups[g].sign &&
+                    groups[q].twbits == groups[g].twbits)
+                    h = q;
+        }
+        if (h == groups.size()) {
+            ++g;
+            continue;
+        }
+        groups[h].idx.insert(groups[h].idx.end(), groups[g].idx.begin(), groups[g].idx.end());
+        groups.erase(groups.begin() + (std::ptrdiff_t)g);
+    }
     for (Group& g : groups) {
         if (g.k0->fused != 0) continue;   // fused kernels have no variants
         int best = 0;
@@ -1469,12 +1495,16 @@ bool launch_level_merged(int count, const wsfft_plan_t* plans, const void* const
                 }
             }
             const PassKernel* k = g.k;
+            bool recorded = false;
             if (g.k0->fused == 0) {
                 std::lock_guard<std::mutex> lk(g_batch_tune_mu);
                 auto it = g_batch_tune.find(key);
                 if (it != g_batch_tune.end()) {
                     const PassKernel* kv = find_pass_kernel(g.kind, g.sign, g.k0->n, g.k0->strided, false, it->second);
-                    if (kv && prepared(kv)) k = kv;
+                    if (kv && prepared(kv)) {
+                        k = kv;
+                        recorded = true;
+                    }
                 }
             }
             BatchTable bt{};
@@ -1544,7 +1574,13 @@ bool launch_level_merged(int count, const wsfft_plan_t* plans, const void* const
                     g_batch_tune[key] = best_v;
                 }
             }
-            const int64_t tiles = fill(k, shared);
+            int64_t tiles = fill(k, shared);
+            // half-width tiles by the same rule as single launches
+            const Pass& P0 = plans[g.idx[c0]]->passes[pi];
+            if (!tune && !recorded && tiles < kFillTiles && P0.narrow_neg && k == (g.sign < 0 ? P0.kern_neg : P0.kern_pos)) {
+                k = g.sign < 0 ? P0.narrow_neg : P0.narrow_pos;
+                tiles = fill(k, shared);
+            }
             if (tiles * k->threads > 0xffffffffLL) return false;
             if (k->launch(shared, &bt, dim3((unsigned)tiles), stream) != hipSuccess) return false;
         }
