@@ -62,7 +62,6 @@ struct Pass {
     float inv_scale;              // the pass's scale in wsfft_execute_inverse
     int outer_dim;                // count whose stride spans whole arrays: 0 = C, 1 = O1, 2 = O2
     int variant;                  // kernel launch variant (autotuner)
-    dim3 grid;
     // half-width tiles for launches too small to fill the chip with the
     // default ones (null: none), same radix plan
     const PassKernel* narrow_neg = nullptr;
@@ -258,12 +257,11 @@ void set_four_step(Pass& A, Pass& B, const AxisGeo& g, int64_t n1, int64_t n2) {
     }
 }
 
-// A direct pass whose columns leave a ragged tile at every outer index (a
-// sixth of a tile or more idle per sixteen columns of work, counted as 6% of
-// the columns) runs its tiles on across the outer indices instead: 96 columns
-// in 64-column tiles 4.3 -> 4.9 TB/s, 288 in 64 5.6 -> 5.9 (2^25 elements);
-// with less waste the ends of rows cost as much as the idle lanes (729
-// columns in 32: no difference).
+// A direct pass whose columns leave a ragged tile at every outer index, idle
+// lanes of 6% or more of the columns, runs its tiles on across the outer
+// indices instead: 96 columns in 64-column tiles 4.3 -> 4.9 TB/s, 288 in 64
+// 5.6 -> 5.9 (2^25 elements); with less waste the ends of rows cost as much as
+// the idle lanes (729 columns in 32, 3%: no difference).
 void flatten(PassArgs& a, int per) {
     if (a.flat_c != 0 || a.O1 <= 1 || a.O2 != 1 || a.C % per == 0 || a.cs_out != 1) return;
     if (a.tw4_mode != 0 || a.tstore != 0 || a.es_in != a.es_out || a.os1_in != a.os1_out) return;
@@ -279,30 +277,77 @@ int64_t blocks_for(const Pass& P, const PassKernel* k) {
     return (a.C + k->per_block - 1) / k->per_block;
 }
 
+// Half-width tiles (variant 2) of the default kernels whose tiles are 64
+// columns wide: the launch takes them when the default tiles are fewer than
+// kFillTiles, two per CU.  Below that, wide tiles leave CUs idle (FP16 96 x
+// 144 x 192 25.5 -> 24.6 us, 256^3 89 -> 84 with the cached passes).
+constexpr int64_t kFillTiles = 512;
+bool set_narrow(Pass& P, StorageKind kind) {
+    if (!P.strided || P.plane || P.four_step == 1 || P.variant != 0 || P.kern_neg->per_block < 64) return true;
+    const int fu = P.kern_neg->fused;
+    if (fu != kFusedNone && fu != kFusedCached) return true;
+    const PassKernel* k[2];
+    for (int i = 0; i < 2; ++i)
+        k[i] = fu == kFusedNone ? find_pass_kernel(kind, i ? 1 : -1, (int)P.n, true, false, 2)
+                                : find_cached_kernel(kind, i ? 1 : -1, (int)P.n, true, fu, 2);
+    if (!k[0] || !k[1] || k[0]->plan != P.kern_neg->plan || k[1]->plan != P.kern_neg->plan) return true;
+    if (k[0]->prepare() != hipSuccess || k[1]->prepare() != hipSuccess) return false;
+    P.narrow_neg = k[0];
+    P.narrow_pos = k[1];
+    return true;
+}
+
+// What one launch of a pass runs: the kernel, its arguments and its tiles.
+// Plan descriptions and the per-plan tuner take it from here as well, so they
+// print and time what is launched.  `a`: the pass's arguments with the call's
+// counts (batch, plane chunk).
+struct PassLaunch {
+    const PassKernel* k;
+    PassArgs a;
+    int64_t tiles;
+};
+PassLaunch pass_launch(const Pass& P, int sign, PassArgs a) {
+    const PassKernel* k = sign < 0 ? P.kern_neg : P.kern_pos;
+    auto tiles = [&] { return ((a.C + k->per_block - 1) / k->per_block) * (P.strided ? a.O1 * a.O2 : 1); };
+    if (P.narrow_neg && tiles() < kFillTiles) k = sign < 0 ? P.narrow_neg : P.narrow_pos;
+    if (P.strided) flatten(a, k->per_block);
+    return {k, a, tiles()};
+}
+// The counts of a launch over zc planes of a chunked pass.
+void chunk_counts(const Pass& P, PassArgs& a, int64_t zc) {
+    if (P.chunk_c > 0) a.C = P.chunk_c * zc;   // C counts the planes' pencils or columns
+    else a.O1 = zc;                           // the outer index counts planes
+}
+
 const char* kind_name(wsfft_dtype_t d, unsigned flags) {
     if (d == WSFFT_C16_FP16 && (flags & WSFFT_FLAG_FP16_MATH)) return "c16-fp16-math";
     return d == WSFFT_C64 ? "c64" : (d == WSFFT_C16_FP16 ? "c16-fp16" : "c16-bf16");
 }
 
-void describe_passes(std::string& out, const std::vector<Pass>& passes) {
+// `zc` > 0: the first two passes run over zc planes per launch.
+void describe_passes(std::string& out, const std::vector<Pass>& passes, int64_t zc = 0) {
     char buf[256];
-    for (const Pass& P : passes) {
-        const int fu = P.kern_neg->fused;
+    for (size_t i = 0; i < passes.size(); ++i) {
+        const Pass& P = passes[i];
+        PassArgs args = P.args;
+        if (zc > 0 && i < 2) chunk_counts(P, args, zc);
+        const PassLaunch L = pass_launch(P, -1, args);
+        const int fu = L.k->fused;
         const char* what = fu == kFusedR2C      ? "r2c"
                            : fu == kFusedC2R    ? "c2r"
                            : fu == kFusedCached ? "cached-"
                            : fu == kFusedCachedStore ? "cached-store-"
                                                 : "";
         if (P.plane) {
-            std::snprintf(buf, sizeof buf, " xy[plane %lldx%lld wg=%d lds=%d grid=%u]", (long long)P.n, (long long)P.n2,
-                          P.kern_neg->threads, P.kern_neg->lds_bytes, P.grid.x);
+            std::snprintf(buf, sizeof buf, " xy[plane %lldx%lld wg=%d lds=%d grid=%lld]", (long long)P.n, (long long)P.n2,
+                          L.k->threads, L.k->lds_bytes, (long long)L.tiles);
             out += buf;
             continue;
         }
-        std::snprintf(buf, sizeof buf, " %c%s[%s%s n=%lld v%d wg=%d per=%d lds=%d grid=%u%s]", "xyz"[P.axis],
+        std::snprintf(buf, sizeof buf, " %c%s[%s%s n=%lld v%d%s wg=%d per=%d lds=%d grid=%lld%s%s]", "xyz"[P.axis],
                       P.four_step == 1 ? "A" : (P.four_step == 2 ? "B" : ""), what, P.strided ? "strided" : "contig",
-                      (long long)P.n, P.variant, P.kern_neg->threads, P.kern_neg->per_block, P.kern_neg->lds_bytes,
-                      P.grid.x, P.args.flat_c ? (P.args.xcd_order ? " flat xcd" : " flat") : (P.args.xcd_order ? " xcd" : ""));
+                      (long long)P.n, P.variant, L.k->variant != P.variant ? " half" : "", L.k->threads, L.k->per_block,
+                      L.k->lds_bytes, (long long)L.tiles, L.a.flat_c ? " flat" : "", L.a.xcd_order ? " xcd" : "");
         out += buf;
     }
 }
@@ -317,7 +362,7 @@ void describe_plan(wsfft_plan_s* plan) {
         std::snprintf(buf, sizeof buf, " (half-spectrum rows %lld apart)", (long long)plan->half_pitch);
         plan->desc.insert(plan->desc.size() - 1, buf);
     }
-    describe_passes(plan->desc, plan->passes);
+    describe_passes(plan->desc, plan->passes, plan->chunk_planes);
     if (plan->chunk_planes > 0) {
         std::snprintf(buf, sizeof buf, " (x, y in chunks of %lld planes)", (long long)plan->chunk_planes);
         plan->desc += buf;
@@ -493,17 +538,19 @@ bool use_variant(wsfft_plan_s* plan, Pass& P, int v) {
     P.kern_neg = kn;
     P.kern_pos = kp;
     P.variant = v;
-    P.grid = dim3((unsigned)blocks);
+    P.narrow_neg = P.narrow_pos = nullptr;
     set_stage_tw(plan, P);
-    return true;
+    return set_narrow(P, kind);
 }
 
 // Median-free best-of timing: microseconds per launch of pass P with variant v.
 double time_variant(wsfft_plan_s* plan, Pass& P, int v, void* buf0, void* buf1, hipStream_t st) {
     Pass Q = P;
     if (!use_variant(plan, Q, v)) return -1.0;
-    const PassKernel* k = plan->sign < 0 ? Q.kern_neg : Q.kern_pos;
-    PassArgs a = Q.args;
+    const PassLaunch L = pass_launch(Q, plan->sign, Q.args);
+    const PassKernel* k = L.k;
+    const dim3 grid((unsigned)L.tiles);
+    PassArgs a = L.a;
     a.src = Q.src_sel == 0 ? buf0 : buf1;
     a.dst = Q.dst_sel == 0 ? buf0 : buf1;
     a.scale = Q.pass_scale;
@@ -515,10 +562,10 @@ double time_variant(wsfft_plan_s* plan, Pass& P, int v, void* buf0, void* buf1, 
     }
     double best = -1.0;
     bool ok = true;
-    for (int i = 0; i < 2 && ok; ++i) ok = k->launch(a, nullptr, Q.grid, st) == hipSuccess;
+    for (int i = 0; i < 2 && ok; ++i) ok = k->launch(a, nullptr, grid, st) == hipSuccess;
     for (int rep = 0; rep < 3 && ok; ++rep) {
         ok = hipEventRecord(e0, st) == hipSuccess;
-        for (int i = 0; i < 3 && ok; ++i) ok = k->launch(a, nullptr, Q.grid, st) == hipSuccess;
+        for (int i = 0; i < 3 && ok; ++i) ok = k->launch(a, nullptr, grid, st) == hipSuccess;
         ok = ok && hipEventRecord(e1, st) == hipSuccess && hipEventSynchronize(e1) == hipSuccess;
         float ms = 0.f;
         if (ok && hipEventElapsedTime(&ms, e0, e1) == hipSuccess) {
@@ -675,26 +722,6 @@ bool use_cached(Pass& P, StorageKind kind, int fused) {
     if (!kn || !kp || kn->per_block != P.kern_neg->per_block || kn->threads != P.kern_neg->threads) return false;
     P.kern_neg = kn;
     P.kern_pos = kp;
-    return true;
-}
-
-// Half-width tiles (variant 2) of the default kernels whose tiles are 64
-// columns wide: the launch takes them when the default tiles are fewer than
-// kFillTiles, two per CU.  Below that, wide tiles leave CUs idle (FP16 96 x
-// 144 x 192 25.5 -> 24.6 us, 256^3 89 -> 84 with the cached passes).
-constexpr int64_t kFillTiles = 512;
-bool set_narrow(Pass& P, StorageKind kind) {
-    if (!P.strided || P.plane || P.four_step == 1 || P.variant != 0 || P.kern_neg->per_block < 64) return true;
-    const int fu = P.kern_neg->fused;
-    if (fu != kFusedNone && fu != kFusedCached) return true;
-    const PassKernel* k[2];
-    for (int i = 0; i < 2; ++i)
-        k[i] = fu == kFusedNone ? find_pass_kernel(kind, i ? 1 : -1, (int)P.n, true, false, 2)
-                                : find_cached_kernel(kind, i ? 1 : -1, (int)P.n, true, fu, 2);
-    if (!k[0] || !k[1] || k[0]->plan != P.kern_neg->plan || k[1]->plan != P.kern_neg->plan) return true;
-    if (k[0]->prepare() != hipSuccess || k[1]->prepare() != hipSuccess) return false;
-    P.narrow_neg = k[0];
-    P.narrow_pos = k[1];
     return true;
 }
 
@@ -895,7 +922,6 @@ static wsfft_plan_t plan_create(int64_t nx, int64_t ny, int64_t nz, int dt, int 
             delete plan;
             return fail(WSFFT_ERROR_UNSUPPORTED_SIZE);
         }
-        P.grid = dim3((unsigned)blocks);
     }
     if (!(flags & WSFFT_FLAG_STREAMING)) {
         apply_cache_policy(plan);
@@ -955,7 +981,7 @@ static wsfft_plan_t plan_create(int64_t nx, int64_t ny, int64_t nz, int dt, int 
         P.args.tw4 = P.tw4_off >= 0 ? plan->tw_dev + P.tw4_off : nullptr;
         // the plane pass's y stage table: the block of its kernel's radix plan
         if (P.plane) P.args.tw4 += (int64_t)P.kern_neg->plan * P.n2;
-        if (P.kern_neg->prepare() != hipSuccess || P.kern_pos->prepare() != hipSuccess) {
+        if (P.kern_neg->prepare() != hipSuccess || P.kern_pos->prepare() != hipSuccess || !set_narrow(P, kind)) {
             (void)hipFree(plan->tw_dev);
             if (plan->work) (void)hipFree(plan->work);
             delete plan;
@@ -963,13 +989,6 @@ static wsfft_plan_t plan_create(int64_t nx, int64_t ny, int64_t nz, int dt, int 
         }
     }
     tune_plan(plan, (flags & WSFFT_FLAG_TUNE) != 0);
-    for (Pass& P : plan->passes)
-        if (!set_narrow(P, kind)) {
-            (void)hipFree(plan->tw_dev);
-            if (plan->work) (void)hipFree(plan->work);
-            delete plan;
-            return fail(WSFFT_ERROR_HIP);
-        }
     describe_plan(plan);
     log_plan(plan->desc);
     {
@@ -1136,7 +1155,6 @@ wsfft_plan_t wsfft_plan_create_real_ex(int64_t nx, int64_t ny, int64_t nz, unsig
                 delete plan;
                 return fail(WSFFT_ERROR_UNSUPPORTED_SIZE);
             }
-            P.grid = dim3((unsigned)blocks);
         }
     if (plan->nsplit > 0) plan->work_bytes = hp * ny * nz * 8;
     int ndev = 0;
@@ -1254,11 +1272,9 @@ bool launch_pass(const wsfft_plan_s* plan, size_t pi, const void* in, void* out,
     const Pass& P = (plan->real && mode != 0) ? plan->cpasses[pi] : plan->passes[pi];
     PassArgs a = P.args;
     const int sign = mode == 0 ? plan->sign : -plan->sign;
-    const PassKernel* k = sign < 0 ? P.kern_neg : P.kern_pos;
     int64_t in_off = 0, out_off = 0;   // bytes
     if (zc > 0) {
-        if (P.chunk_c > 0) a.C = P.chunk_c * zc;   // C counts the planes' pencils or columns
-        else a.O1 = zc;                           // the outer index counts planes
+        chunk_counts(P, a, zc);
         in_off = z0 * P.plane_in;
         out_off = z0 * P.plane_out;
     }
@@ -1267,12 +1283,9 @@ bool launch_pass(const wsfft_plan_s* plan, size_t pi, const void* in, void* out,
         else if (P.outer_dim == 1) a.O1 *= batch;
         else a.O2 *= batch;
     }
-    auto tiles = [&] { return ((a.C + k->per_block - 1) / k->per_block) * (P.strided ? a.O1 * a.O2 : 1); };
-    if (P.narrow_neg && tiles() < kFillTiles) k = sign < 0 ? P.narrow_neg : P.narrow_pos;
-    if (P.strided) flatten(a, k->per_block);
-    const int64_t blocks = tiles();
-    if (blocks * k->threads > 0xffffffffLL) return false;
-    const dim3 grid((unsigned)blocks);
+    const PassLaunch L = pass_launch(P, sign, a);
+    a = L.a;
+    if (L.tiles * L.k->threads > 0xffffffffLL) return false;
     auto sel = [&](int s) -> void* {
         return s == 0 ? const_cast<void*>(in) : (s == 1 ? out : plan->work);
     };
@@ -1282,7 +1295,7 @@ bool launch_pass(const wsfft_plan_s* plan, size_t pi, const void* in, void* out,
     if (keep && P.src_sel == 0 && pi > 0) a.src = keep;
     if (keep && P.dst_sel == 0) a.dst = keep;
     a.scale = mode == 2 ? P.inv_scale : P.pass_scale;
-    return k->launch(a, nullptr, grid, stream) == hipSuccess;
+    return L.k->launch(a, nullptr, dim3((unsigned)L.tiles), stream) == hipSuccess;
 }
 
 // A kernel's function attributes (its dynamic LDS limit), set once per kernel
