@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 CONTIG = {108: 9.395e-08, 486: 1.176e-07, 576: 1.075e-07, 648: 1.144e-07, 729: 1.218e-07, 972: 1.211e-07,
           1296: 1.187e-07, 1728: 1.177e-07, 2187: 1.331e-07, 3888: 1.347e-07, 4374: 1.398e-07, 6561: 1.464e-07,
           7776: 1.407e-07, 8748: 1.433e-07}
-STRIDED = {324: 1.097e-07, 576: 1.102e-07, 864: 1.138e-07}
+STRIDED = {324: 1.097e-07, 576: 1.102e-07, 864: 1.138e-07, 1024: 1.091e-07}
 SLACK = 1.005
 
 
