@@ -134,12 +134,12 @@ constexpr int cfg_K_strided(int N, int bytes, int plan = 0, int vb = 8) {
 // 4733/4609, 486 3120/3050 -> 4700/4521, 576 3673/3465 -> 4914/4460, 648
 // 3440/3348 -> 4742/4682, 729 3545/3403 -> 4593/4560, 768 3861/3685 ->
 // 4915/4764, 864 2799/2713 -> 4407/4084, 972 2581/2538 -> 4167/4170, 1024
-// 4686/3630 -> 5047/3855.  No complex64 entry rounds more than the rule's
+// 4567/3733 -> 4786/4019 (half width 5077/3948, cfg_half).  No complex64 entry rounds more than the rule's
 // radix schedule: the relative error of single passes against FP64 (2^21 values
 // per length, 0.2% between seeds) grew by 3.4% at 576 points in four stages
 // instead of three, 2.4% at 864 in 27 x 32 and 2.1% at 324 in 18 x 18, so these
 // keep the rule's radices (5019/4481, 4781/4348 and 5510/4968 GB/s without that
-// condition).  256 points keep the rule's tile with the exchange
+// condition; 1024 in 32 x 32 instead of 4 x 16 x 16 is level, see Dft<32>).  256 points keep the rule's tile with the exchange
 // in two rounds, four workgroups per CU instead of two: 5499/5142 ->
 // 5436/5145 at 256 MiB, 5071/4802 -> 5512/5317 at 64.  (Complex64 tiles of
 // 128 and 256 points in 64 columns gained 4-7% there but leave the chip short
@@ -154,7 +154,7 @@ constexpr StridedGeo kStrided8[] = {   // complex64
     {72, 9, 32, 1, 0},   {81, 9, 32, 1, 0},   {162, 9, 32, 1, 0},  {216, 6, 32, 2, 0},
     {243, 9, 32, 3, 0},  {256, 8, 32, 2, 1},  {288, 18, 32, 1, 0}, {324, 12, 16, 2, 1},
     {432, 12, 16, 2, 1}, {486, 27, 16, 2, 1}, {576, 16, 16, 3, 1}, {648, 27, 16, 2, 0}, {729, 27, 16, 3, 0},
-    {768, 32, 16, 3, 1}, {864, 24, 16, 3, 1}, {972, 27, 16, 2, 0}, {1024, 32, 16, 2, 0}};
+    {768, 32, 16, 3, 1}, {864, 24, 16, 3, 1}, {972, 27, 16, 2, 0}, {1024, 16, 32, 2, 0}};
 constexpr StridedGeo kStrided4[] = {   // 4-byte storage, FP32 values
     {48, 8, 32, 1, 0},   {64, 8, 64, 1, 0},   {72, 9, 32, 1, 0},   {81, 9, 64, 1, 0},
     {96, 4, 64, 2, 0},   {108, 12, 32, 1, 0},  {128, 8, 64, 2, 0},  {144, 12, 64, 1, 0},  {162, 9, 64, 2, 0},
@@ -166,6 +166,26 @@ constexpr StridedGeo kStrided4m[] = {   // 4-byte storage, FP16 values
     {162, 9, 64, 1, 0},  {192, 4, 64, 1, 0},  {216, 6, 64, 1, 0},  {288, 8, 64, 1, 0},  {324, 18, 32, 1, 0},
     {384, 8, 64, 3, 0},  {432, 24, 32, 1, 0}, {486, 18, 32, 1, 0}, {576, 24, 32, 1, 0}, {648, 14, 32, 2, 0},
     {729, 27, 32, 3, 0}, {768, 16, 32, 2, 1}, {864, 16, 32, 2, 0}, {972, 27, 32, 2, 0}, {1024, 16, 64, 4, 0}};
+
+// Half-width tile of the default strided kernel (variant 2): the same with half
+// the columns, or the measured one.  The 1024-point complex64 tile holds a CU by
+// itself (135 KB of LDS), two of its half-width ones of 32 threads share one.
+// Where the rows of an array are less than kNearRows bytes apart those are
+// faster, beyond that their 128-byte rows cost more (GB/s, full / half width, by the
+// distance of the rows over 2 GiB and 256 MiB: 8 KB 4963/5254 and 4869/5072, 16
+// KB 5076/5135 and 4989/4838, 32 KB 4843/5014 and 4773/4994, 48 KB of 6144 x
+// 1024 x 16, y and the cached x together 924/882 us, 64 KB 4830/4428 and 4897/4545, 256 KB 3955/3758 and 4028/3926, 8 MB over 8 GiB 4393/3859; the
+// rule's tile at 8 MB 3961).
+constexpr int kNearRows = 64 * 1024;
+constexpr StridedGeo cfg_half(StridedGeo g, int bytes) {
+    if (bytes == 8 && g.n == 1024) return {1024, 32, 16, 2, 0};
+    if (g.P > 1) g.P /= 2;
+    return g;
+}
+// Whether a tile holds a CU by itself and halves to whole cache lines, and
+// whether a launch may halve it (set_narrow).
+constexpr bool cfg_alone(int lds, int P, int bytes) { return lds > kLdsBytesMax / 2 && P / 2 * bytes >= 128; }
+constexpr bool cfg_halves(int lds, int P, int bytes) { return P >= 64 || cfg_alone(lds, P, bytes); }
 
 // Exchange rounds of a split axis's first pass: its FP64 twiddle recurrence
 // restarts in every round, so powers of two take the fewest rounds that leave

@@ -62,10 +62,10 @@ struct Pass {
     float inv_scale;              // the pass's scale in wsfft_execute_inverse
     int outer_dim;                // count whose stride spans whole arrays: 0 = C, 1 = O1, 2 = O2
     int variant;                  // kernel launch variant (autotuner)
-    // half-width tiles for launches too small to fill the chip with the
-    // default ones (null: none), same radix plan
+    // half-width tiles, same radix plan (null: none), where halve() takes them
     const PassKernel* narrow_neg = nullptr;
     const PassKernel* narrow_pos = nullptr;
+    bool alone = false, near_rows = false;   // default tiles of one per CU; rows less than kNearRows apart
     bool plane = false;           // fused x + y pass over whole planes (n = nx, n2 = ny;
     int64_t n2 = 0;               // tw_off / tw4_off: the x / y stage tables)
     // plane chunks (Infinity Cache policy): C per xy-plane (0: O1 counts the
@@ -277,15 +277,24 @@ int64_t blocks_for(const Pass& P, const PassKernel* k) {
     return (a.C + k->per_block - 1) / k->per_block;
 }
 
-// Half-width tiles (variant 2) of the default kernels whose tiles are 64
-// columns wide: the launch takes them when the default tiles are fewer than
+// Half-width tiles (variant 2) of the default kernels.  Tiles of 64 columns:
+// the launch takes the half-width ones when the default tiles are fewer than
 // kFillTiles, two per CU.  Below that, wide tiles leave CUs idle (FP16 96 x
-// 144 x 192 25.5 -> 24.6 us, 256^3 89 -> 84 with the cached passes).
+// 144 x 192 25.5 -> 24.6 us, 256^3 89 -> 84 with the cached passes).  Tiles
+// that hold a CU by themselves: where rows are near each other (kNearRows), and
+// where the last round of tiles over the CUs would idle an eighth of the launch
+// (z of 324 x 27 x 1024, 274 tiles: 42 us, half-width 32).
 constexpr int64_t kFillTiles = 512;
+constexpr int64_t kCus = 256;
+bool halve(const Pass& P, int64_t tiles) {
+    if (!P.narrow_neg) return false;
+    if (!P.alone) return tiles < kFillTiles;
+    return P.near_rows || ((tiles + kCus - 1) / kCus * kCus - tiles) * 8 > tiles;
+}
 bool set_narrow(Pass& P, StorageKind kind) {
-    if (!P.strided || P.plane || P.four_step == 1 || P.variant != 0 || P.kern_neg->per_block < 64) return true;
-    const int fu = P.kern_neg->fused;
-    if (fu != kFusedNone && fu != kFusedCached) return true;
+    const int fu = P.kern_neg->fused, eb = kind == kC64 ? 8 : 4;
+    if (!P.strided || P.plane || P.four_step == 1 || P.variant != 0 || (fu != kFusedNone && fu != kFusedCached)) return true;
+    if (!cfg_halves(P.kern_neg->lds_bytes, P.kern_neg->per_block, eb)) return true;
     const PassKernel* k[2];
     for (int i = 0; i < 2; ++i)
         k[i] = fu == kFusedNone ? find_pass_kernel(kind, i ? 1 : -1, (int)P.n, true, false, 2)
@@ -294,6 +303,8 @@ bool set_narrow(Pass& P, StorageKind kind) {
     if (k[0]->prepare() != hipSuccess || k[1]->prepare() != hipSuccess) return false;
     P.narrow_neg = k[0];
     P.narrow_pos = k[1];
+    P.alone = P.kern_neg->per_block < 64;
+    P.near_rows = P.alone && P.args.es_in * eb < kNearRows;
     return true;
 }
 
@@ -309,7 +320,7 @@ struct PassLaunch {
 PassLaunch pass_launch(const Pass& P, int sign, PassArgs a) {
     const PassKernel* k = sign < 0 ? P.kern_neg : P.kern_pos;
     auto tiles = [&] { return ((a.C + k->per_block - 1) / k->per_block) * (P.strided ? a.O1 * a.O2 : 1); };
-    if (P.narrow_neg && tiles() < kFillTiles) k = sign < 0 ? P.narrow_neg : P.narrow_pos;
+    if (halve(P, tiles())) k = sign < 0 ? P.narrow_neg : P.narrow_pos;
     if (P.strided) flatten(a, k->per_block);
     return {k, a, tiles()};
 }
@@ -539,6 +550,7 @@ bool use_variant(wsfft_plan_s* plan, Pass& P, int v) {
     P.kern_pos = kp;
     P.variant = v;
     P.narrow_neg = P.narrow_pos = nullptr;
+    P.alone = P.near_rows = false;
     set_stage_tw(plan, P);
     return set_narrow(P, kind);
 }
@@ -1361,6 +1373,7 @@ bool launch_level_merged(int count, const wsfft_plan_t* plans, const void* const
         StorageKind kind;
         int sign;
         unsigned twbits;
+        bool near_rows;                // Pass::near_rows
         int votes[kMaxVariants];
         std::vector<int> idx;
         const PassKernel* k;           // the kernel the group runs
@@ -1376,10 +1389,10 @@ bool launch_level_merged(int count, const wsfft_plan_t* plans, const void* const
         Group* g = nullptr;
         for (Group& q : groups)
             if (q.k0->n == k->n && q.k0->n2 == k->n2 && q.k0->strided == k->strided && q.k0->fused == k->fused &&
-                q.kind == kind && q.sign == sign && q.twbits == twbits)
+                q.kind == kind && q.sign == sign && q.twbits == twbits && q.near_rows == P.near_rows)
                 g = &q;
         if (!g) {
-            groups.push_back({k, kind, sign, twbits, {}, {}, k});
+            groups.push_back({k, kind, sign, twbits, P.near_rows, {}, {}, k});
             g = &groups.back();
         }
         if (k->variant >= 0 && k->variant < kMaxVariants) ++g->votes[k->variant];
@@ -1467,7 +1480,7 @@ bool launch_level_merged(int count, const wsfft_plan_t* plans, const void* const
             for (size_t q = 0; q < groups.size() && bytes <= kJoinBytes; ++q)
                 if (groups[q].k0->fused == kFusedCached && groups[q].k0->n == groups[g].k0->n && groups[q].k0->strided &&
                     groups[q].kind == groups[g].kind && groups[q].sign == groups[g].sign &&
-                    groups[q].twbits == groups[g].twbits)
+                    groups[q].twbits == groups[g].twbits && groups[q].near_rows == groups[g].near_rows)
                     h = q;
         }
         if (h == groups.size()) {
@@ -1590,7 +1603,7 @@ bool launch_level_merged(int count, const wsfft_plan_t* plans, const void* const
             int64_t tiles = fill(k, shared);
             // half-width tiles by the same rule as single launches
             const Pass& P0 = plans[g.idx[c0]]->passes[pi];
-            if (!tune && !recorded && tiles < kFillTiles && P0.narrow_neg && k == (g.sign < 0 ? P0.kern_neg : P0.kern_pos)) {
+            if (!tune && !recorded && halve(P0, tiles) && k == (g.sign < 0 ? P0.kern_neg : P0.kern_pos)) {
                 k = g.sign < 0 ? P0.narrow_neg : P0.narrow_pos;
                 tiles = fill(k, shared);
             }
