@@ -127,7 +127,10 @@ typedef enum {
 /*
  * Autotuning.  Passes of the hot lengths (powers of two up to 1024 strided,
  * 16384 contiguous) have several compiled launch variants (radix schedule,
- * tile width).  With WSFFT_FLAG_TUNE or the environment WSFFT_TUNE=1, plan
+ * tile width).  Passes that go through the caches (WSFFT_FLAG_STREAMING above:
+ * by array size, or over rows of no whole cache lines) have one and are not
+ * tuned, neither here nor by wsfft_tune_batched or WSFFT_TUNE_FORCE; with
+ * WSFFT_FLAG_STREAMING every pass of a hot length is.  With WSFFT_FLAG_TUNE or the environment WSFFT_TUNE=1, plan
  * creation picks, per pass geometry, the variant recorded in the tuning cache
  * ($WSFFT_TUNE_CACHE, else $HOME/.cache/wsfft_tune.txt), or times every
  * variant of uncached geometries with HIP events on two temporary device

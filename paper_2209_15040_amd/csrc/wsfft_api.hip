@@ -25,6 +25,7 @@
 #include <fstream>
 #include <map>
 #include <mutex>
+#include <new>
 #include <set>
 #include <sstream>
 #include <string>
@@ -1911,14 +1912,18 @@ wsfft_status_t wsfft_execute_many(wsfft_plan_t plan, const void* in, void* out, 
             if (!launch_pass(plan, pi, in, out, adjoint ? 1 : 0, stream, count)) return WSFFT_ERROR_HIP;
         return WSFFT_SUCCESS;
     }
-    const std::vector<wsfft_plan_t> plans((size_t)count, plan);
-    std::vector<const void*> ins((size_t)count);
-    std::vector<void*> outs((size_t)count);
-    for (int i = 0; i < count; ++i) {
-        ins[i] = reinterpret_cast<const void*>(i0 + span * (uintptr_t)i);
-        outs[i] = reinterpret_cast<void*>(o0 + span * (uintptr_t)i);
+    try {   // no exception leaves a C entry
+        const std::vector<wsfft_plan_t> plans((size_t)count, plan);
+        std::vector<const void*> ins((size_t)count);
+        std::vector<void*> outs((size_t)count);
+        for (int i = 0; i < count; ++i) {
+            ins[i] = reinterpret_cast<const void*>(i0 + span * (uintptr_t)i);
+            outs[i] = reinterpret_cast<void*>(o0 + span * (uintptr_t)i);
+        }
+        return batched(count, plans.data(), ins.data(), outs.data(), adjoint, stream, false);
+    } catch (const std::bad_alloc&) {
+        return WSFFT_ERROR_OUT_OF_MEMORY;
     }
-    return batched(count, plans.data(), ins.data(), outs.data(), adjoint, stream, false);
 }
 
 wsfft_status_t wsfft_tune_batched(int count, const wsfft_plan_t* plans, const void* const* in, void* const* out,
