@@ -3,26 +3,25 @@
 //   T  threads per pencil          P  pencils (contiguous layout) or
 //   K  LDS exchange rounds            columns (strided layout) per workgroup
 //
-// Rules measured on MI355X at N = 512 (512^3 arrays):
+// Rules for the lengths that the measured tables below (kStrided*, kContig*) do
+// not list, and for the tuner's radix variant:
 // * strided tiles of 32 columns: 256-byte rows for complex64, 128-byte rows
-//   for the 4-byte types (these carry half the bytes and do better with
-//   narrower tiles than with 64 columns);
-// * strided complex64 tiles run best with radix <= 16 stages (plan 1), the
-//   4-byte types with the fewest stages (plan 0);
-// * 32 elements per thread, the exchange split into rounds of up to ~72 KB
-//   of LDS, so two workgroups stay resident per CU and one's transform and
+//   for the 4-byte types; 64 columns up to 64 points;
+// * strided complex64 tiles take radix <= 16 stages (plan 1), the 4-byte types
+//   the fewest stages (plan 0);
+// * up to 32 elements per thread, the exchange split into rounds of up to ~72
+//   KB of LDS, so two workgroups stay resident per CU and one's transform and
 //   store drain overlap the other's loads;
 // * contiguous pencils: N/16 threads each where the widest stage leaves
-//   every thread a butterfly (512 points: 16 threads x 32 elements, radix
-//   32 x 16, for complex64; 32 threads x 16 elements, radix 8 x 8 x 8, for
-//   the 4-byte types), 256-thread workgroups (one wave for the 4-byte types
-//   and for 1024-point complex64), and paired (two-element) first-stage
+//   every thread a butterfly, 256-thread workgroups (one wave for the 4-byte
+//   types and for 1024-point complex64), and paired (two-element) first-stage
 //   loads where the stage allows them;
-// * non-temporal (streaming) loads and stores help every pass.
+// * non-temporal (streaming) loads and stores, unless the cache policies of
+//   wsfft_api.hip choose others.
 // FP16 storage with FP16 arithmetic (4-byte register and LDS values, argument
 // vb = 4) holds half the state per element: strided tiles of 64 columns
-// (256-byte rows) with twice the elements per thread, exchange rounds of at
-// most ~36 KB, and 256-thread contiguous tiles.
+// (256-byte rows) for powers of two with twice the elements per thread,
+// exchange rounds of at most ~36 KB, and 256-thread contiguous tiles.
 #pragma once
 #include "fft_device.hpp"
 
@@ -123,9 +122,9 @@ constexpr int cfg_K_strided(int N, int bytes, int plan = 0, int vb = 8) {
 // under radix <= 16, and tiles of 24 .. 48 elements per thread hold one
 // workgroup per CU at 150-210 VGPRs, or spill.  So: the two-stage schedule
 // with radices up to 32 (plan 0) where it exists and keeps a butterfly per
-// thread in both stages, T a divisor of both butterfly counts, and from 432
-// points on 16-column tiles (128-byte rows of complex64) with two or more
-// workgroups per CU.  Every (T, P, K, plan) with at most 16% idle lanes was
+// thread in both stages, T a divisor of the butterfly counts or near one, and
+// from 432 points on 16-column tiles (128-byte rows of complex64) with two or
+// more workgroups per CU.  Every (T, P, K, plan) with at most 16% idle lanes was
 // timed over a y-like (columns of one plane) and a z-like array of 256 and 64
 // MiB; an entry is the best of the four together and stands where it gains 2%
 // or more.  GB/s (y / z, 256 MiB complex64), rule -> entry: 162 4806/4433 ->
@@ -134,19 +133,22 @@ constexpr int cfg_K_strided(int N, int bytes, int plan = 0, int vb = 8) {
 // 4733/4609, 486 3120/3050 -> 4700/4521, 576 3673/3465 -> 4914/4460, 648
 // 3440/3348 -> 4742/4682, 729 3545/3403 -> 4593/4560, 768 3861/3685 ->
 // 4915/4764, 864 2799/2713 -> 4407/4084, 972 2581/2538 -> 4167/4170, 1024
-// 4567/3733 -> 4786/4019 (half width 5077/3948, cfg_half).  No complex64 entry rounds more than the rule's
-// radix schedule: the relative error of single passes against FP64 (2^21 values
-// per length, 0.2% between seeds) grew by 3.4% at 576 points in four stages
-// instead of three, 2.4% at 864 in 27 x 32 and 2.1% at 324 in 18 x 18, so these
-// keep the rule's radices (5019/4481, 4781/4348 and 5510/4968 GB/s without that
-// condition; 1024 in 32 x 32 instead of 4 x 16 x 16 is level, see Dft<32>).  256 points keep the rule's tile with the exchange
-// in two rounds, four workgroups per CU instead of two: 5499/5142 ->
-// 5436/5145 at 256 MiB, 5071/4802 -> 5512/5317 at 64.  (Complex64 tiles of
-// 128 and 256 points in 64 columns gained 4-7% there but leave the chip short
-// of workgroups on 128^3 and the half spectra of 256^3, which lost 2-6%.)  The
-// 4-byte types gain 3-40% (864: 2.7x) the same way; FP16 values hold half the
-// state and keep the wider tiles.  (Launches of few 64-column tiles take
-// half-width ones, wsfft_api.hip.)
+// 4567/3733 -> 4786/4019 (half width 5077/3948, cfg_half).
+// No complex64 entry rounds more than the rule's radix schedule: the relative
+// error of single passes against FP64 (2^21 values per length, 0.2% between
+// seeds) grew by 3.4% at 576 points in four stages instead of three, 2.4% at 864
+// in 27 x 32 and 2.1% at 324 in 18 x 18, so these keep the rule's radices
+// (5019/4481, 4781/4348 and 5510/4968 GB/s without that condition; 1024 in
+// 32 x 32 instead of 4 x 16 x 16 is level, see Dft<32>).  Storage of 16 bits
+// rounds far more than any schedule: its entries may take other stages (768
+// points 8 x 8 x 12 instead of 24 x 32).
+// 256 points keep the rule's tile with the exchange in two rounds, four
+// workgroups per CU instead of two: 5499/5142 -> 5436/5145 at 256 MiB,
+// 5071/4802 -> 5512/5317 at 64.  (Complex64 tiles of 128 and 256 points in 64
+// columns gained 4-7% there but leave the chip short of workgroups on 128^3 and
+// the half spectra of 256^3, which lost 2-6%.)  The 4-byte types gain 3-40%
+// (864: 2.7x) the same way; FP16 values hold half the state and keep the wider
+// tiles.  (Launches of few 64-column tiles take half-width ones, wsfft_api.hip.)
 struct StridedGeo {
     int n, T, P, K, plan;
 };
@@ -200,7 +202,10 @@ constexpr int cfg_K_four_step(int N, int P, int K, int vb) {
 // Exchange rounds of the strided kernel that streams past the caches: 256
 // points of complex64 take one (second pass of 65536 x 1024: 184.7 us, two
 // rounds 194.5; y axis of 512x256x512: 186.8 and 194.1), where the cached and
-// fused kernels of smaller arrays take the two of the table.
+// fused kernels of smaller arrays take the two of the table (256^3 Poisson 331
+// us, one round 345).  Both sides are measured; the cause is not resolved: two
+// rounds hold four workgroups per CU instead of two and wait at one barrier
+// more.
 constexpr int cfg_K_stream(int N, int bytes, int K) { return N == 256 && bytes == 8 ? 1 : K; }
 
 // Geometry of the default strided kernel: the measured entry, else the rules.
@@ -227,8 +232,7 @@ constexpr StridedGeo cfg_strided(int N, int bytes, int vb) {
 // write the same line several times (27 points 1.2 TB/s, 81 points 1.3, 108
 // points 1.2, 32 points 3.5).  Staged tiles (kFlagStage) move the tile's rows
 // as one contiguous range through LDS, whole lines per wave, for two more LDS
-// trips per element; the rest of an entry is as in the strided tables (T a
-// divisor of the stages' butterflies, 64 .. 512 threads).  Direct and staged
+// trips per element; the rest of an entry is as in the strided tables.  Direct and staged
 // tiles of every (T, P, plan) were timed at 256 and 32 MiB; staged wins on
 // short and radix-3 lengths, direct from about 500 points on where pencils
 // are whole lines.  GB/s at 256 MiB of complex64, rule -> entry: 16 3236 ->
@@ -287,12 +291,17 @@ constexpr ContigGeo kContig4m[] = {   // 4-byte storage, FP16 values
     {729, 81, 3, 1, false},  {768, 32, 2, 1, false},  {864, 32, 2, 0, false},  {1024, 32, 8, 0, false},
     {2048, 64, 1, 0, false}};
 
-// Exchange rounds of the default contiguous complex64 kernel: two for the long
-// pencils whose LDS then lets two or three workgroups share a CU instead of
-// one or two (GB/s at 1 GiB, one round -> two: 5184 4601 -> 5415, 9216 4828 ->
-// 5461, 10368 3755 -> 4508, 11664 3640 -> 4083, 12288 3788 -> 4396, 13122 3600
-// -> 3969; 6561, an odd length, three: 4158 -> 4517).  The half-spectrum passes need their whole pencil in LDS and keep
-// the rules' geometry at these lengths.
+// Exchange rounds of the default contiguous complex64 kernel.  From 5184 points
+// on a whole pencil's LDS (8 bytes a point and padding) lets one to three
+// workgroups share a CU; where the registers would let more, and the kernel
+// needs no more of them for it, the exchange runs in rounds of a part of the
+// pencil.  GB/s, one round -> two: 5184 4601 -> 5415, 9216 4828 -> 5461, 10368
+// 3755 -> 4508, 11664 3640 -> 4083, 12288 3788 -> 4396, 13122 3600 -> 3969 (1
+// GiB), and three, 6561 being odd: 4158 -> 4517.  Where the registers hold as
+// few workgroups as the LDS, rounds gain nothing or spend more registers: 7776
+// 4073 -> 3604 (135 -> 174 VGPRs), 4374 4333 -> 4241 (256 MiB).  The
+// half-spectrum passes need their whole pencil in LDS and keep the rules'
+// geometry at these lengths.
 constexpr int cfg_K_contig(int N, int bytes) {
     if (bytes == 8 && N == 6561) return 3;
     return bytes == 8 && (N == 5184 || N == 9216 || N == 10368 || N == 11664 || N == 12288 || N == 13122) ? 2 : 1;
