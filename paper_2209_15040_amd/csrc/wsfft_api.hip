@@ -309,21 +309,20 @@ bool set_narrow(Pass& P, StorageKind kind) {
     return true;
 }
 
-// What one launch of a pass runs: the kernel, its arguments and its tiles.
-// Plan descriptions and the per-plan tuner take it from here as well, so they
-// print and time what is launched.  `a`: the pass's arguments with the call's
-// counts (batch, plane chunk).
+// What one launch of a pass runs: the kernel, its tiles and, in `a`, its
+// arguments, from those of the pass with the call's counts (batch, plane
+// chunk).  Plan descriptions and the per-plan tuner take it from here as well,
+// so they print and time what is launched.
 struct PassLaunch {
     const PassKernel* k;
-    PassArgs a;
     int64_t tiles;
 };
-PassLaunch pass_launch(const Pass& P, int sign, PassArgs a) {
+PassLaunch pass_launch(const Pass& P, int sign, PassArgs& a) {
     const PassKernel* k = sign < 0 ? P.kern_neg : P.kern_pos;
     auto tiles = [&] { return ((a.C + k->per_block - 1) / k->per_block) * (P.strided ? a.O1 * a.O2 : 1); };
     if (halve(P, tiles())) k = sign < 0 ? P.narrow_neg : P.narrow_pos;
     if (P.strided) flatten(a, k->per_block);
-    return {k, a, tiles()};
+    return {k, tiles()};
 }
 // The counts of a launch over zc planes of a chunked pass.
 void chunk_counts(const Pass& P, PassArgs& a, int64_t zc) {
@@ -359,7 +358,7 @@ void describe_passes(std::string& out, const std::vector<Pass>& passes, int64_t 
         std::snprintf(buf, sizeof buf, " %c%s[%s%s n=%lld v%d%s wg=%d per=%d lds=%d grid=%lld%s%s]", "xyz"[P.axis],
                       P.four_step == 1 ? "A" : (P.four_step == 2 ? "B" : ""), what, P.strided ? "strided" : "contig",
                       (long long)P.n, P.variant, L.k->variant != P.variant ? " half" : "", L.k->threads, L.k->per_block,
-                      L.k->lds_bytes, (long long)L.tiles, L.a.flat_c ? " flat" : "", L.a.xcd_order ? " xcd" : "");
+                      L.k->lds_bytes, (long long)L.tiles, args.flat_c ? " flat" : "", args.xcd_order ? " xcd" : "");
         out += buf;
     }
 }
@@ -560,10 +559,10 @@ bool use_variant(wsfft_plan_s* plan, Pass& P, int v) {
 double time_variant(wsfft_plan_s* plan, Pass& P, int v, void* buf0, void* buf1, hipStream_t st) {
     Pass Q = P;
     if (!use_variant(plan, Q, v)) return -1.0;
-    const PassLaunch L = pass_launch(Q, plan->sign, Q.args);
+    PassArgs a = Q.args;
+    const PassLaunch L = pass_launch(Q, plan->sign, a);
     const PassKernel* k = L.k;
     const dim3 grid((unsigned)L.tiles);
-    PassArgs a = L.a;
     a.src = Q.src_sel == 0 ? buf0 : buf1;
     a.dst = Q.dst_sel == 0 ? buf0 : buf1;
     a.scale = Q.pass_scale;
@@ -726,8 +725,9 @@ namespace {
 // The 16-bit storage types have no contiguous kernels with cached loads; 64
 // MiB <= A < 128 MiB: cached x stores, cached y and z passes (FP16 256^3 89.4
 // -> 83.8 us, with FP16 arithmetic 84.7 -> 71.6, 512 x 512 x 64 88.7 -> 81.3;
-// at 32 MiB 45 -> 49 and at 512 MiB 611 -> 672, so not there); beyond, the
-// last two rules.  The cached kernels have the launch geometry of the default
+// at 32 MiB 45 -> 49 and at 512 MiB 611 -> 672, so not there; 384^3, 216 MiB,
+// would gain, 308 -> 271, but arrays of 128 MiB and more keep the schedule they
+// had); beyond, the last two rules.  The cached kernels have the launch geometry of the default
 // ones, so the results are bitwise equal.
 bool use_cached(Pass& P, StorageKind kind, int fused) {
     const PassKernel* kn = find_cached_kernel(kind, -1, (int)P.n, P.strided, fused);
@@ -1297,7 +1297,6 @@ bool launch_pass(const wsfft_plan_s* plan, size_t pi, const void* in, void* out,
         else a.O2 *= batch;
     }
     const PassLaunch L = pass_launch(P, sign, a);
-    a = L.a;
     if (L.tiles * L.k->threads > 0xffffffffLL) return false;
     auto sel = [&](int s) -> void* {
         return s == 0 ? const_cast<void*>(in) : (s == 1 ? out : plan->work);
