@@ -271,9 +271,7 @@ template <int SIGN> struct Dft<16, SIGN> : DftComp<4, 4, SIGN> {};
 template <int SIGN> struct Dft<18, SIGN> : DftComp<2, 9, SIGN> {};
 template <int SIGN> struct Dft<24, SIGN> : DftComp<8, 3, SIGN> {};
 template <int SIGN> struct Dft<27, SIGN> : DftComp<3, 9, SIGN> {};
-// 1024 points as 32 x 32, relative error against FP64: 1.0914e-7 with fine
-// eighth turns, 1.1050e-7 without (4 x 16 x 16: 1.0913e-7).
-template <int SIGN> struct Dft<32, SIGN> : DftComp<8, 4, SIGN, true> {};
+template <int SIGN> struct Dft<32, SIGN> : DftComp<8, 4, SIGN> {};
 
 // ------------------------------------------------------ stage schedule ---
 struct Radices {
@@ -815,6 +813,11 @@ struct PencilPass {
         else IO::template st<NTS>(b, off, v);
     }
     static constexpr Radices RD = make_radices(N, PLAN);
+    // 1024 points of complex64 in strided tiles take 32 x 32 with fine eighth
+    // turns, relative error against FP64 1.0914e-7; without them 1.1050e-7, in 4
+    // x 16 x 16, three stages, 1.0913e-7.  (In the 16 x 16 x 32 of 8192 contiguous
+    // points they would cost 0.7% of an 8192 x 8192 image.)
+    static constexpr bool FINE = STRIDED && N == 1024 && IO::bytes == 8;
     static constexpr int NS = RD.n;
     static constexpr int ROWS = N / K;   // LDS rows per exchange round
     // LDS layout: strided tiles store [element][column] with one V of
@@ -928,7 +931,8 @@ struct PencilPass {
                     u[r] = cmul(u[r], w);
                 }
             }
-            Dft<Q::R, SIGN>::run(u);
+            if constexpr (FINE && Q::R == 32) DftComp<8, 4, SIGN, true>::run(u);
+            else Dft<Q::R, SIGN>::run(u);
         }
     }
 

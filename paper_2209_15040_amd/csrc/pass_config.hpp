@@ -139,7 +139,7 @@ constexpr int cfg_K_strided(int N, int bytes, int plan = 0, int vb = 8) {
 // seeds) grew by 3.4% at 576 points in four stages instead of three, 2.4% at 864
 // in 27 x 32 and 2.1% at 324 in 18 x 18, so these keep the rule's radices
 // (5019/4481, 4781/4348 and 5510/4968 GB/s without that condition; 1024 in
-// 32 x 32 instead of 4 x 16 x 16 is level, see Dft<32>).  Storage of 16 bits
+// 32 x 32 instead of 4 x 16 x 16 is level, see PencilPass::FINE).  Storage of 16 bits
 // rounds far more than any schedule: its entries may take other stages (768
 // points 8 x 8 x 12 instead of 24 x 32).
 // 256 points keep the rule's tile with the exchange in two rounds, four
